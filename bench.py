@@ -166,7 +166,8 @@ def cpu_baseline(V, n_f, seconds, way, seed=123):
 CSRC = os.path.join(ROOT, "paper_1705_08210_amd", "csrc")
 _VALU_SOURCES = ["ps_internal.h", "mgemm_core.h", "mgemm_kernels.h", "mg_common.hip",
                  "mg_f32.hip", "mg_f16.hip", "mg_u8.hip", "policy.hip"]
-_MFMA_SOURCES = ["ps_internal.h", "mfma.hip", "policy.hip"]
+_MFMA_SOURCES = ["ps_internal.h", "mfma_tile.h", "mfma.hip", "policy.hip"]
+_BITS_SOURCES = ["ps_internal.h", "mfma_tile.h", "bitplane.hip", "policy.hip"]
 KERNEL_SOURCES = {
     "ps_mg2_kernel": _VALU_SOURCES,
     "ps_mg3f_kernel": _VALU_SOURCES,
@@ -174,7 +175,8 @@ KERNEL_SOURCES = {
     "ps_mfma2_lv_kernel": _MFMA_SOURCES,
     "ps_mfma2_lvd_kernel": _MFMA_SOURCES,
     "ps_mfma2_kernel": _MFMA_SOURCES,
-    "ps_mfma2_dma_kernel": _MFMA_SOURCES,
+    "ps_bp2_kernel": _BITS_SOURCES,
+    "ps_bp3_kernel": _BITS_SOURCES,
     "ps_mfma3_lv_kernel": _MFMA_SOURCES,
     "ps_mfma3_lvs_kernel": _MFMA_SOURCES,
     "ps_mfma3_lvsd_kernel": _MFMA_SOURCES,
@@ -488,12 +490,12 @@ def measure(args, wl, K, W, with_cpu=True):
                               "whole_call_ms": round(full_ms, 3),
                               "whole_call_cmp_per_s": n_f * m / (full_ms * 1e-3)}
         path = resolved_path(args, V, 2)
-        if path == "bits":   # v_and + v_bcnt per 32 comparisons
+        if path == "bits" and (args.tile or N):   # v_and + v_bcnt per 32 comparisons
             dtype, bound, ops_per_cmp, peak = "b1", "alu", 2.0 / 32, HALF_RATE_OPS_TOPS
             kernel = "ps_mg2_kernel"
-        elif path == "mfma_fp4":   # e2m1 planes, FP32 sums
+        elif path in ("mfma_fp4", "bits"):   # planes of bits as e2m1 operands, FP32 sums
             dtype, bound, ops_per_cmp, peak = "fp4", "mfma", 2.0 * levels, FP4_MFMA_PEAK_TOPS
-            kernel = "ps_mfma2_dma_kernel"
+            kernel = "ps_bp2_kernel"
         elif path == "mfma":   # thermometer levels: `levels` int8 MACs (2 ops) per comparison
             dtype, bound, ops_per_cmp, peak = "u8", "mfma", 2.0 * levels, INT8_MFMA_PEAK_TOPS
             kernel = ("ps_mfma2_kernel" if args.tile == 2 else
@@ -583,9 +585,9 @@ def measure(args, wl, K, W, with_cpu=True):
 
         cmp = n_f * math.comb(n_v, 3)
         path = resolved_path(args, V, 3)
-        if path == "mfma_fp4":   # e2m1 planes: `levels` MACs per comparison
+        if path in ("mfma_fp4", "bits"):   # planes of bits: `levels` MACs per comparison
             dtype, bound, ops_per_cmp, peak = "fp4", "mfma", 2.0 * levels, FP4_MFMA_PEAK_TOPS
-            kernel = "ps_mfma3_kernel"
+            kernel = "ps_bp3_kernel"
         elif path == "mfma":
             dtype, bound, ops_per_cmp, peak = "u8", "mfma", 2.0 * levels, INT8_MFMA_PEAK_TOPS
             # opts.tile 2: per-slab tiles; else the split tiling (pairs x vectors)

@@ -95,8 +95,10 @@ typedef enum {
 
 /* Compute path for the pair numerators. */
 typedef enum {
-    PS_PATH_AUTO = 0,    /* U8 with 1 <= levels <= 15 and rows within the MFMA
-                            limits below: MFMA; otherwise VALU */
+    PS_PATH_AUTO = 0,    /* U8 with 1 <= levels <= 15: MFMA_FP4 (triangles of
+                            more than 1024 vectors and the 3-way slices), MFMA
+                            where that does not apply, each within its limits
+                            below; otherwise VALU */
     PS_PATH_VALU = 1,    /* register-blocked min/add on the vector ALUs */
     PS_PATH_MFMA = 2,    /* alias PS_PATH_MFMA_THERMO.  U8 only:
                             min(a,b) = sum_{t=1..levels} [a>=t][b>=t], an
@@ -114,15 +116,19 @@ typedef enum {
                             per value for int8, half a byte for FP4) and 256
                             plane rows must span < 2^31 bytes.  Beyond these
                             limits: PS_ERR_UNSUPPORTED */
-    PS_PATH_MFMA_FP4 = 3, /* U8 only: the same 0/1 planes as FP4 (e2m1) operands
-                            of the scaled matrix-core instruction, FP32
-                            accumulation (exact: sums are integers < 2^24,
-                            needs levels * n_f < 2^24); needs levels >= max(V) */
+    PS_PATH_MFMA_FP4 = 3, /* U8 only: the same 0/1 planes, one bit per value in the
+                            workspace, expanded in registers to FP4 (e2m1)
+                            operands of the matrix cores, FP32 accumulation
+                            (exact: sums are integers < 2^24, needs levels *
+                            n_f < 2^24); needs levels >= max(V) */
     PS_PATH_BITS = 4     /* U8 binary data, values in {0, 1} (opts.levels = 1):
                             the Sorensen special case of Section 2.3, where min
-                            is AND.  The fields are packed 32 to a word and a
-                            word pair costs an AND and a population count;
-                            exact integer sums.  2-way and 3-way.  Values above
+                            is AND.  The fields are packed 32 to a word; with
+                            opts.tile = 0 and n_f < 2^24 the words feed the
+                            matrix cores as for MFMA_FP4, else (and for
+                            ps2_compute_shard) a word pair costs an AND and a
+                            population count on the vector ALUs; exact integer
+                            sums either way.  2-way and 3-way.  Values above
                             1 are outside this path's domain (results
                             unspecified). */
 } ps_path;
@@ -221,10 +227,11 @@ size_t ps3_workspace_size(int32_t dtype, int64_t n_f, int64_t n_v,
  *          or NULL to compute them into the workspace
  *   opts   path VALU, BITS (binary U8 data, X_j = V AND v_j), or for U8
  *          data the MFMA paths, exact: a pair's row is staged as the
- *          bytewise min of its two vectors and thresholded per level,
- *          [min(a,b) >= t][c >= t] = [min(a,b,c) >= t]; the int8 path tiles
- *          the stage as pairs x vectors (ps_tile_config, way 3); AUTO picks
- *          as for ps2_compute
+ *          bytewise min of its two vectors and thresholded per level (as the
+ *          AND of their bit planes on the FP4 path),
+ *          [min(a,b) >= t][c >= t] = [min(a,b,c) >= t]; the stage is tiled
+ *          as pairs x vectors (ps_tile_config, way 3, for the int8 path);
+ *          AUTO picks as for ps2_compute
  *   c3     device float; receives the triples of [j_begin, j_end) packed in
  *          j-slab order starting at offset 0 (i.e. at global index
  *          off(j_begin))
@@ -245,7 +252,8 @@ ps_status ps3_compute(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
  * holds from the library's first use there until the process ends.  The
  * array of the calling thread's current device is used, so `stream` must
  * belong to that device.
- *   Scratch need: the value of ps3_workspace_size() for the same arguments.
+ *   Scratch need: the value of ps3_workspace_size() for the same arguments
+ *   (path AUTO runs without bit planes where they would not fit).
  *   With s and n2 given and n_f <= 4096 it is a few tens of KB; computing
  *   the pair numerators inside takes C(n_v, 2) values plus field-chunk
  *   partials.  A call that needs more than PS_NOALLOC_SCRATCH_BYTES returns

@@ -105,7 +105,10 @@ def tune_paths(ways=(2, 3), reps=3, quick=False, log=print):
                 run = (lambda p: ps.ps3(V, s=s, n2=n2, c3=c3, path=p, levels=LEVELS))
             names = list(PATH_CODES)
             times = [_time(lambda p=p: run(p), reps) for p in names]
-            best = names[int(np.argmin(times))]
+            # small triangles keep the paths that need no plane workspace
+            cand = [k for k, p in enumerate(names)
+                    if not (way == 2 and NV_BUCKETS[vb][1] <= 1024 and p == "mfma_fp4")]
+            best = names[min(cand, key=lambda k: times[k])]
             rec = _entry("u8", way, "auto", fb, vb, (n_f, n_v), PATH_CODES[best], times)
             log(json.dumps(rec))
             out.append(rec)

@@ -8,62 +8,51 @@
 // paper's min-product (Section 3.1) recast so that the matrix cores can run
 // it.
 //
-// Two operand formats, one kernel structure:
-//   int8: one plane value per byte, v_mfma_i32_32x32x32_i8, int32 sums;
-//   fp4 : two plane values per byte (e2m1: 0 -> 0x0, 1 -> 0x2),
-//         v_mfma_scale_f32_32x32x64_f8f6f4 with unit scales, FP32 sums
-//         (exact: every partial sum is an integer below 2^24).
-// Kernels:
+// One plane value per byte, v_mfma_i32_32x32x32_i8, int32 sums.  The planes are
+// formed in registers from V's bytes (the fused kernels further down) or, for
+// the 4x4 wave layout and for 8 and more levels beyond 2^24, written to the
+// workspace first:
 //   ps_thermo_expand_kernel  V (uint8, n_v x ld) -> planes P, row length
 //                            L * kpad fields, kpad = n_f rounded up to whole
 //                            field tiles; HBM-bound, one pass.
-//   ps_mfma2_kernel          upper-triangle tiles of P P^T, FP64 epilogue
-//                            (int8: operands staged through registers);
-//   ps_mfma2_dma_kernel      the same with operands loaded straight into LDS
-//                            (fp4);
+//   ps_mfma2_kernel          upper-triangle tiles of P P^T, FP64 epilogue;
 //   ps_mfma3_kernel          3-way slices: (P_i AND P_j) P_k^T over the
 //                            rectangles i < j < k, raw n3' out.
+// (Planes of one bit per value on the fp4 matrix cores: bitplane.hip.)
 #include <type_traits>
 
-#include "ps_internal.h"
+#include "mfma_tile.h"
 
 namespace ps {
 
-typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
-typedef int v4i_t __attribute__((ext_vector_type(4)));
-typedef int v8i_t __attribute__((ext_vector_type(8)));
-typedef int v16i_t __attribute__((ext_vector_type(16)));
-typedef float v16f_t __attribute__((ext_vector_type(16)));
-
-enum { kFmtI8 = 0, kFmtF4 = 1 };
-__host__ __device__ constexpr int fields_per_byte(int fmt) { return fmt == kFmtF4 ? 2 : 1; }
-
-constexpr int kMB = kMfmaTile;   // output tile rows and columns
 constexpr int kPad = 16;      // LDS row padding: b128 reads of 32 rows spread over the banks
 constexpr int kTileBytes = 128;   // plane rows are padded to whole multiples of this
 
 // Field-tile depth in plane bytes.  A deeper tile gives each staged load
-// more MFMA work to hide behind; int8 with 8 waves fits 128 bytes (two
-// 147 KB LDS buffers, no spills), the fp4 and 4-wave variants run out of
-// registers there and keep 64.
-template <int FMT, int WN>
-__host__ __device__ constexpr int mfma_mk() { return (FMT == kFmtI8 && WN == 2) ? 128 : 64; }
+// more MFMA work to hide behind; 8 waves fit 128 bytes (two 147 KB LDS
+// buffers, no spills), the 4-wave variant runs out of registers there and
+// keeps 64.
+template <int WN>
+__host__ __device__ constexpr int mfma_mk() { return WN == 2 ? 128 : 64; }
 #ifndef PS_MFMA_GROUP
 #define PS_MFMA_GROUP 4
 #endif
 constexpr int kGroup = PS_MFMA_GROUP;   // tile columns per L2-sharing group (grouped_tri_decode;
                                         // 4 measured 1-2% faster than 1, 2, 8, 16, 32)
 
-// Fields of one plane row, padded to whole kTileBytes-byte field tiles
-// (a multiple of every variant's tile depth; >= 1 tile).
-static int64_t plane_fields(int64_t n_f, int fmt) {
-    const int64_t q = (int64_t)kTileBytes * fields_per_byte(fmt);
+// Fields of one plane row, padded to whole kTileBytes-byte field tiles (a
+// multiple of every variant's tile depth; >= 1 tile) of `fpb` fields per byte.
+static int64_t plane_fields(int64_t n_f, int fpb = 1) {
+    const int64_t q = (int64_t)kTileBytes * fpb;
     const int64_t kpad = (n_f + q - 1) / q * q;
     return kpad > 0 ? kpad : q;
 }
 
+// fmt 1 (the FP4 path): half a byte per value, the size of the path's workspace
+// and of its row limit; its planes of bits need a quarter of it.
 int64_t mfma_row_bytes(int64_t n_f, int levels, int fmt) {
-    return (int64_t)levels * (plane_fields(n_f, fmt) / fields_per_byte(fmt));
+    const int fpb = fmt == 1 ? 2 : 1;
+    return (int64_t)levels * (plane_fields(n_f, fpb) / fpb);
 }
 
 size_t mfma_workspace_bytes(int64_t n_f, int64_t n_v, int levels, int fmt, int wide) {
@@ -80,22 +69,13 @@ __device__ __forceinline__ uint32_t ge_bytes(uint32_t x, uint32_t t) {
     return (((x | 0x80808080u) - t * 0x01010101u) >> 7) & 0x01010101u;
 }
 
-// fp4 packing of four 0/1 bytes (one word of ge_bytes) into four nibbles
-__device__ __forceinline__ uint32_t nibbles_e2m1(uint32_t m) {
-    return ((m & 0x1u) << 1) | ((m & 0x100u) >> 3) | ((m & 0x10000u) >> 7) |
-           ((m & 0x1000000u) >> 11);
-}
-
 // One thread per 32 fields of one vector; kpad is a multiple of 128.
-template <int FMT>
 __global__ __launch_bounds__(256) void ps_thermo_expand_kernel(const uint8_t* V, int64_t n_f,
                                                                int64_t n_v, int64_t ld,
                                                                int levels, int64_t kpad,
                                                                int8_t* P) {
-    constexpr int FPB = fields_per_byte(FMT);
     const int64_t nch = kpad / 32;
     const int64_t total = n_v * nch;
-    const int64_t plane_bytes = kpad / FPB;
     const bool vec = ((uintptr_t)V % 16 == 0) && (ld % 16 == 0);
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
          t += (int64_t)gridDim.x * blockDim.x) {
@@ -111,25 +91,16 @@ __global__ __launch_bounds__(256) void ps_thermo_expand_kernel(const uint8_t* V,
             for (int e = 0; e < 32; ++e)
                 if (q0 + e < n_f) u.b[e] = src[e];
         }
-        int8_t* dst = P + row * (int64_t)levels * plane_bytes + q0 / FPB;
+        int8_t* dst = P + row * (int64_t)levels * kpad + q0;
         for (int lev = 1; lev <= levels; ++lev) {
-            int8_t* d = dst + (int64_t)(lev - 1) * plane_bytes;
-            if constexpr (FMT == kFmtI8) {
-                uint4 o0, o1;
-                o0.x = ge_bytes(u.w[0], lev); o0.y = ge_bytes(u.w[1], lev);
-                o0.z = ge_bytes(u.w[2], lev); o0.w = ge_bytes(u.w[3], lev);
-                o1.x = ge_bytes(u.w[4], lev); o1.y = ge_bytes(u.w[5], lev);
-                o1.z = ge_bytes(u.w[6], lev); o1.w = ge_bytes(u.w[7], lev);
-                *(uint4*)d = o0;
-                *(uint4*)(d + 16) = o1;
-            } else {
-                uint4 o;
-                o.x = nibbles_e2m1(ge_bytes(u.w[0], lev)) | (nibbles_e2m1(ge_bytes(u.w[1], lev)) << 16);
-                o.y = nibbles_e2m1(ge_bytes(u.w[2], lev)) | (nibbles_e2m1(ge_bytes(u.w[3], lev)) << 16);
-                o.z = nibbles_e2m1(ge_bytes(u.w[4], lev)) | (nibbles_e2m1(ge_bytes(u.w[5], lev)) << 16);
-                o.w = nibbles_e2m1(ge_bytes(u.w[6], lev)) | (nibbles_e2m1(ge_bytes(u.w[7], lev)) << 16);
-                *(uint4*)d = o;
-            }
+            int8_t* d = dst + (int64_t)(lev - 1) * kpad;
+            uint4 o0, o1;
+            o0.x = ge_bytes(u.w[0], lev); o0.y = ge_bytes(u.w[1], lev);
+            o0.z = ge_bytes(u.w[2], lev); o0.w = ge_bytes(u.w[3], lev);
+            o1.x = ge_bytes(u.w[4], lev); o1.y = ge_bytes(u.w[5], lev);
+            o1.z = ge_bytes(u.w[6], lev); o1.w = ge_bytes(u.w[7], lev);
+            *(uint4*)d = o0;
+            *(uint4*)(d + 16) = o1;
         }
     }
 }
@@ -158,21 +129,6 @@ struct MfmaArgs {
 // waves of 2 x 2 blocks, two workgroups per CU.
 template <int WN, int TB = kMB>
 __host__ __device__ constexpr int mfma_threads() { return 64 * 2 * (TB / (32 * WN)); }
-
-// n / d correctly rounded, for integers 0 <= n < 2^24 and 1 <= d < 2^24 held
-// in floats (the FP32 quotients of Section 2.1 and Eq. 1): the reciprocal
-// refinement and the two remainder corrections of the IEEE division
-// sequence, without its range scaling and special-case fix-up.  No
-// operand, reciprocal, partial quotient or remainder here is denormal,
-// infinite or needs scaling, so those steps are identities and the result
-// is the sequence's own, the correctly rounded quotient.
-__device__ __forceinline__ float div_u24(float n, float d) {
-    const float y0 = __builtin_amdgcn_rcpf(d);
-    const float y = __builtin_fmaf(__builtin_fmaf(-d, y0, 1.0f), y0, y0);
-    const float q0 = n * y;
-    const float q1 = __builtin_fmaf(__builtin_fmaf(-d, q0, n), y, q0);
-    return __builtin_fmaf(__builtin_fmaf(-d, q1, n), y, q1);
-}
 
 // Epilogue of one wave's 4 x WN blocks of 32 x 32 (Section 2.1): n2 exact,
 // c2 = 2 n2 / (s_i + s_j) in FP64, rounded once to FP32, d = 0 gives 0.
@@ -215,17 +171,9 @@ __device__ __forceinline__ void mfma_epilogue(const AccT (&acc)[4][WN], const Mf
     }
 }
 
-// Dword 3 of a raw buffer descriptor on gfx950: 32-bit data format, offset
-// addressing, no swizzle (loads past num_records return zero).
-constexpr int kRsrcWord3 = 0x00020000;
-
-// Accumulator type of a format.
-template <int FMT>
-using mfma_acc_t = typename std::conditional<FMT == kFmtF4, v16f_t, v16i_t>::type;
-
 // LDS of the register-staged tile: two buffers for each of the two operands.
-template <int FMT, int WN, int TB = kMB>
-constexpr int mfma_lds_bytes() { return 4 * TB * (mfma_mk<FMT, WN>() + kPad); }
+template <int WN, int TB = kMB>
+constexpr int mfma_lds_bytes() { return 4 * TB * (mfma_mk<WN>() + kPad); }
 
 // Main loop of one register-staged TB x TB tile: A rows a0 .. a0+TB-1 and
 // B rows b0 .. b0+TB-1 of the planes (rows at or past n_v read as zero); with
@@ -234,16 +182,16 @@ constexpr int mfma_lds_bytes() { return 4 * TB * (mfma_mk<FMT, WN>() + kPad); }
 // Field tile kt+1 is written from registers into the second LDS buffer while
 // tile kt is consumed, one barrier per field tile; tile kt+2 is loaded into
 // registers meanwhile (a second register set, loading two tiles ahead, was
-// measured slower on int8).  The loads are buffer loads with 32-bit offsets
-// (measured 12% faster on int8 than 64-bit addresses with row tests).  Waves
+// measured slower).  The loads are buffer loads with 32-bit offsets
+// (measured 12% faster than 64-bit addresses with row tests).  Waves
 // that are not `active` take part in staging and barriers only.
-template <int FMT, int WN, bool MASK, int TB = kMB>
+template <int WN, bool MASK, int TB = kMB>
 __device__ __forceinline__ void mfma_tile(const MfmaArgs& a, int64_t a0, int64_t b0,
                                           const int8_t* mrow, bool active, int wr, int wc,
-                                          mfma_acc_t<FMT> (&acc)[TB / 64][WN], int8_t* lds) {
+                                          v16i_t (&acc)[TB / 64][WN], int8_t* lds) {
     constexpr int WM = TB / 64;                    // 32-row blocks per wave
     constexpr int kMThreads = mfma_threads<WN, TB>();
-    constexpr int kMK = mfma_mk<FMT, WN>();
+    constexpr int kMK = mfma_mk<WN>();
     constexpr int kPitch = kMK + kPad;
     constexpr int kRowChunks = kMK / 16;           // 16-byte chunks per tile row
     constexpr int kStage = TB * kRowChunks / kMThreads;   // 16-byte chunks per thread per operand
@@ -257,7 +205,7 @@ __device__ __forceinline__ void mfma_tile(const MfmaArgs& a, int64_t a0, int64_t
 #pragma unroll
     for (int m = 0; m < WM; ++m)
 #pragma unroll
-        for (int n = 0; n < WN; ++n) acc[m][n] = (mfma_acc_t<FMT>){};
+        for (int n = 0; n < WN; ++n) acc[m][n] = (v16i_t){};
 
     // staging: TB rows x kMK bytes per operand, kRowChunks threads per row.
     // Buffer resources over the tile's A and B rows (the host checks that 256
@@ -325,25 +273,17 @@ __device__ __forceinline__ void mfma_tile(const MfmaArgs& a, int64_t a0, int64_t
 #pragma unroll
             for (int m = 0; m < WM; ++m)
 #pragma unroll
-                for (int n = 0; n < WN; ++n) {
-                    if constexpr (FMT == kFmtI8) {
-                        acc[m][n] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[m], fb[n],
-                                                                          acc[m][n], 0, 0, 0);
-                    } else {  // 64 e2m1 values per row per k-step, unit (2^0) scales
-                        const v8i_t xa = {fa[m].x, fa[m].y, fa[m].z, fa[m].w, 0, 0, 0, 0};
-                        const v8i_t xb = {fb[n].x, fb[n].y, fb[n].z, fb[n].w, 0, 0, 0, 0};
-                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                            xa, xb, acc[m][n], 4, 4, 0, 127, 0, 127);
-                    }
-                }
+                for (int n = 0; n < WN; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[m], fb[n], acc[m][n], 0,
+                                                                      0, 0);
         }
         // tile kt+1 into the other buffer (after the last tile the write is
         // stale and never read; unconditional, so it joins this block)
         store(cur ^ 1);
-        // schedule (measured 5% faster on int8): the next k-step's fragment
+        // schedule (measured 5% faster): the next k-step's fragment
         // reads between the MFMAs of this one, the staging writes of the
         // next field tile between the MFMAs of the last k-step
-        if constexpr (FMT == kFmtI8 && WN == 2 && kMK == 128) {
+        if constexpr (WN == 2 && kMK == 128) {
             constexpr int R = WM + WN, M = WM * WN, W = 2 * kStage;   // per k-step / tile
             static_assert(M >= R && W % M == 0, "schedule pattern");
             __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
@@ -379,9 +319,9 @@ __device__ __forceinline__ void mfma_tile(const MfmaArgs& a, int64_t a0, int64_t
     }
 }
 
-template <int FMT, int WN>
+template <int WN>
 __global__ __launch_bounds__(mfma_threads<WN>(), 1) void ps_mfma2_kernel(MfmaArgs a) {
-    __shared__ __attribute__((aligned(16))) int8_t lds[mfma_lds_bytes<FMT, WN>()];
+    __shared__ __attribute__((aligned(16))) int8_t lds[mfma_lds_bytes<WN>()];
     const int64_t t = a.item0 + (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) +
                       blockIdx.x / kXcds;
     if (t >= a.ntiles) return;
@@ -393,8 +333,8 @@ __global__ __launch_bounds__(mfma_threads<WN>(), 1) void ps_mfma2_kernel(MfmaArg
     const int wc = (wave / 2) * 32 * WN;    // i offset (B rows)
     // some i < j with both < n_v among rows j0+wr.. and columns i0+wc..?
     const bool active = (i0 + wc < a.n_v) && (j0 + wr < a.n_v) && (i0 + wc + 1 < j0 + wr + 128);
-    mfma_acc_t<FMT> acc[4][WN];
-    mfma_tile<FMT, WN, false>(a, j0, i0, nullptr, active, wr, wc, acc, lds);
+    v16i_t acc[4][WN];
+    mfma_tile<WN, false>(a, j0, i0, nullptr, active, wr, wc, acc, lds);
     if (!active) return;
     mfma_epilogue<WN>(acc, a, i0, j0, wr, wc, lane);
 }
@@ -412,10 +352,10 @@ __global__ __launch_bounds__(mfma_threads<WN>(), 1) void ps_mfma2_kernel(MfmaArg
 // tiles, TB = 128 over the rest (two workgroups per CU, so one workgroup's
 // waves that lie outside the rectangle leave their SIMD to the other's).
 // ---------------------------------------------------------------------------
-template <int FMT, int TB>
+template <int TB>
 __global__ __launch_bounds__((mfma_threads<2, TB>()), kMB / TB) void ps_mfma3_kernel(MfmaArgs a) {
     constexpr int WN = 2, WM = TB / 64;
-    __shared__ __attribute__((aligned(16))) int8_t lds[mfma_lds_bytes<FMT, WN, TB>()];
+    __shared__ __attribute__((aligned(16))) int8_t lds[mfma_lds_bytes<WN, TB>()];
     const int64_t t = a.item0 + (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) +
                       blockIdx.x / kXcds;
     if (t >= a.ntiles) return;
@@ -433,8 +373,8 @@ __global__ __launch_bounds__((mfma_threads<2, TB>()), kMB / TB) void ps_mfma3_ke
     const int wr = (wave % 2) * (TB / 2);   // k offset of the wave's block (A rows)
     const int wc = (wave / 2) * 32 * WN;    // i offset (B rows)
     const bool active = (k0 + wr < a.n_v) && (i0 + wc < j);
-    mfma_acc_t<FMT> acc[WM][WN];
-    mfma_tile<FMT, WN, true, TB>(a, k0, i0, a.P + j * a.kp, active, wr, wc, acc, lds);
+    v16i_t acc[WM][WN];
+    mfma_tile<WN, true, TB>(a, k0, i0, a.P + j * a.kp, active, wr, wc, acc, lds);
     if (!active) return;
     const int64_t base = slab_offset(a.n_v, j) - slab_offset(a.n_v, a.j_begin);
     const int64_t ib = i0 + wc + (lane % 32);
@@ -482,31 +422,6 @@ constexpr int kLvMK = 128;   // fields per field tile (one byte each)
 enum { kLvPerm = 0, kLvSub = 1 };
 
 __host__ __device__ constexpr int lv_mode(int levels) { return levels <= 7 ? kLvPerm : kLvSub; }
-
-struct LvArgs {
-    const uint8_t* V;
-    int64_t ld, n_f, n_v;
-    int levels;
-    int group;            // 2-way: block columns per tile-order group
-    int64_t nk;           // field tiles
-    const double* s;
-    float* c2;
-    int32_t* n2;
-    int64_t nb, ntiles;
-    // 3-way
-    int64_t j_begin, j_end;
-    const int64_t* prefix;
-    uint32_t* c3;
-    int64_t item0;
-    int32_t mode, ob;
-    int32_t f32div;       // the quotient's operands are integers below 2^24 (FP32 division)
-    // split 3-way tiling, part p = 0, 1: its tiles, row tiles, the prefix of
-    // their column-tile counts, and its pairs [r_begin, r_end) (colex indices
-    // for the (i, j) part, lex indices for the (j, k) part); tiles
-    // [0, nt[0]) of a launch are part 0's, the next nt[1] part 1's
-    int64_t nt[2], nrt[2], r_begin[2], r_end[2];
-    const int64_t* pre[2];
-};
 
 // Bytewise min of a and b given d, a word whose byte k has bit 7 set exactly
 // where byte k of a is at least byte k of b: the flags widen to 0xff bytes
@@ -1109,227 +1024,6 @@ __global__ __launch_bounds__((mfma_threads<2, TB>()), kMB / TB) void ps_mfma3_lv
 // ones and are never stored (a wave with none skips the multiply-adds).
 // ---------------------------------------------------------------------------
 
-// Part 0 epilogue (Eq. 1 as in lv3_epilogue): a lane's two columns are pairs
-// (i, j) with their own j, so n2(j, k) is gathered per element like n2(i, k);
-// 2 s_k of the tile's rows is staged in LDS.  Stores go through a buffer
-// resource from the tile's first entry (0, jmin, k0) to the end of the last
-// pair's slab; an element outside i < j < k < n_v gets an offset past it.
-template <bool F32>
-__device__ __forceinline__ void lvs_epilogue0(const LvArgs& a, const v16i_t (&acc)[4][2],
-                                              int64_t p0, int64_t k0, int wr, int wc,
-                                              bool active, int8_t* lds) {
-    using R = typename std::conditional<F32, float, double>::type;
-    constexpr int TB = kMB, WN = 2, WM = 4;
-    const int lane = threadIdx.x % 64;
-    const int64_t n = a.n_v;
-    const double* __restrict__ S = a.s;
-    const int32_t* __restrict__ N2 = a.n2;
-    R* rs2 = (R*)lds;   // 2 s_k
-    if (threadIdx.x < TB) {
-        const int64_t k = k0 + threadIdx.x;
-        rs2[threadIdx.x] = k < n ? (R)(2.0 * S[k]) : (R)0;
-    }
-    __syncthreads();
-    if (!active) return;
-    const int64_t pe = a.r_end[0];
-    const int64_t jmin = pair_j(p0);
-    const int64_t jlast = pair_j(p0 + TB - 1 < pe ? p0 + TB - 1 : pe - 1);
-    const int64_t ob = slab_offset(n, a.j_begin);
-    const int64_t base0 = slab_offset(n, jmin) - ob + (k0 - jmin - 1) * jmin;
-    const __amdgpu_buffer_rsrc_t rc3 = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.c3 + base0), (short)0, (int)((slab_offset(n, jlast + 1) - ob - base0) * 4),
-        kRsrcWord3);
-    const __amdgpu_buffer_rsrc_t rn2 = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)N2, (short)0, (int)(n * (n - 1) / 2 * 4), kRsrcWord3);
-    R ls2[WN];            // 2 (s_i + s_j)
-    uint32_t nij[WN];     // n2(i, j)
-    int ii[WN], jj[WN];   // the column's pair; jj = n_v when past the part
-    uint32_t sb[WN];      // entry (i, j, k) - base0 = sb + k j (mod 2^32)
-#pragma unroll
-    for (int nn = 0; nn < WN; ++nn) {
-        const int64_t p = p0 + wc + nn * 32 + lane % 32;
-        const bool vp = p < pe;
-        const int64_t pp = vp ? p : pe - 1;
-        const int64_t j = pair_j(pp), i = pp - j * (j - 1) / 2;
-        ls2[nn] = (R)2 * ((R)S[i] + (R)S[j]);
-        nij[nn] = (uint32_t)N2[pp];
-        ii[nn] = (int)i;
-        jj[nn] = vp ? (int)j : (int)n;
-        sb[nn] = (uint32_t)(slab_offset(n, j) - ob - base0 - (j + 1) * j + i);
-    }
-    constexpr int RB = 4, NB = WM * 16 / RB;
-    auto row_dk = [&](int b, int q) {
-        const int m = b / (16 / RB), r = (b % (16 / RB)) * RB + q;
-        return wr + m * 32 + (r / 4) * 8 + (lane / 32) * 4 + (r % 4);
-    };
-    struct Batch {
-        uint32_t nik[RB][WN], njk[RB][WN];
-    };
-    const int kb = (int)k0;
-    auto load_batch = [&](int b, Batch& o) {
-#pragma unroll
-        for (int q = 0; q < RB; ++q) {
-            const uint32_t k = (uint32_t)(kb + row_dk(b, q));
-            const uint32_t ck = (k * (k - 1)) >> 1;   // k < 2^16: the table is below 2^31 bytes
-#pragma unroll
-            for (int nn = 0; nn < WN; ++nn) {
-                o.nik[q][nn] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                    rn2, (int)((ck + (uint32_t)ii[nn]) * 4), 0, 0);
-                o.njk[q][nn] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                    rn2, (int)((ck + (uint32_t)jj[nn]) * 4), 0, 0);
-            }
-        }
-    };
-    auto store_batch = [&](int b, const Batch& o) {
-        const int m = b / (16 / RB);
-#pragma unroll
-        for (int q = 0; q < RB; ++q) {
-            const int r = (b % (16 / RB)) * RB + q;
-            const int dk = row_dk(b, q);
-            const int k = kb + dk;
-            const R rk = rs2[dk];
-#pragma unroll
-            for (int nn = 0; nn < WN; ++nn) {
-                const bool ok = k > jj[nn] && k < (int)n;
-                const uint32_t n3 = nij[nn] + o.nik[q][nn] + o.njk[q][nn] - (uint32_t)acc[m][nn][r];
-                const R d = ls2[nn] + rk;
-                const R dd = d > (R)0 ? d : (R)1;
-                float qv;
-                if constexpr (F32)
-                    qv = div_u24((float)(3u * n3), dd);
-                else
-                    qv = (float)((3.0 * (double)n3) / dd);
-                const float c = d > (R)0 ? qv : 0.0f;
-                const uint32_t off = ok ? (sb[nn] + __umul24((uint32_t)k, (uint32_t)jj[nn])) * 4u
-                                        : 0x80000000u;
-                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, c), rc3,
-                                                      (int)off, 0, 0);
-            }
-        }
-    };
-    Batch bt[2];
-    load_batch(0, bt[0]);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        if (b + 1 < NB) load_batch(b + 1, bt[(b + 1) & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-        store_batch(b, bt[b & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// Part 1 epilogue (TB rows): a row is a pair (j, k); its 2 (s_j + s_k), n2(j, k), the
-// pair-table offsets of rows j and k, j and its output row offset are staged
-// in LDS once per tile; n2(i, j) and n2(i, k) are gathered per element
-// (contiguous in i).  Stores from the tile's first pair's entry i = 0 to the
-// end of the last pair's slab; columns i >= j get an offset past it.
-template <bool F32, int TB>
-__device__ __forceinline__ void lvs_epilogue1(const LvArgs& a, const v16i_t (&acc)[4][2],
-                                              int64_t q0, int64_t i0, int wr, int wc,
-                                              bool active, int8_t* lds) {
-    using R = typename std::conditional<F32, float, double>::type;
-    constexpr int WN = 2, WM = 4;   // TB rows (pairs) from q0
-    const int lane = threadIdx.x % 64;
-    const int64_t n = a.n_v;
-    const double* __restrict__ S = a.s;
-    const int32_t* __restrict__ N2 = a.n2;
-    const int64_t qe = a.r_end[1];
-    const int64_t ob = slab_offset(n, a.j_begin);
-    int64_t jf, kf, jl, kl;
-    lex_pair(n, q0 < qe ? q0 : qe - 1, jf, kf);   // (a half past the part stores nothing)
-    lex_pair(n, q0 + TB - 1 < qe ? q0 + TB - 1 : qe - 1, jl, kl);
-    const int64_t base0 = slab_offset(n, jf) - ob + (kf - jf - 1) * jf;
-    int4* rowi = (int4*)lds;                         // {c(j), c(k), j, output row offset}
-    R* rs2 = (R*)(lds + TB * sizeof(int4));           // 2 (s_j + s_k)
-    int32_t* rnj = (int32_t*)(lds + TB * (sizeof(int4) + sizeof(R)));   // n2(j, k)
-    if (threadIdx.x < TB) {
-        const int64_t q = q0 + threadIdx.x;
-        const bool vq = q < qe;
-        int64_t j, k;
-        lex_pair(n, vq ? q : qe - 1, j, k);
-        const int64_t cj = j * (j - 1) / 2, ck = k * (k - 1) / 2;
-        rowi[threadIdx.x] = make_int4((int)cj, (int)ck, vq ? (int)j : 0,
-                                      (int)(slab_offset(n, j) - ob + (k - j - 1) * j - base0));
-        rs2[threadIdx.x] = (R)2 * ((R)S[j] + (R)S[k]);
-        rnj[threadIdx.x] = N2[ck + j];
-    }
-    __syncthreads();
-    if (!active) return;
-    const __amdgpu_buffer_rsrc_t rc3 = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.c3 + base0), (short)0, (int)((slab_offset(n, jl + 1) - ob - base0) * 4),
-        kRsrcWord3);
-    const __amdgpu_buffer_rsrc_t rn2 = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)N2, (short)0, (int)(n * (n - 1) / 2 * 4), kRsrcWord3);
-    R ls[WN];        // 2 s_i
-    int ii[WN];
-#pragma unroll
-    for (int nn = 0; nn < WN; ++nn) {
-        const int64_t i = i0 + wc + nn * 32 + lane % 32;
-        ls[nn] = (R)(2.0 * S[i < n ? i : n - 1]);
-        ii[nn] = (int)i;
-    }
-    constexpr int RB = 4, NB = WM * 16 / RB;
-    auto row_dk = [&](int b, int q) {
-        const int m = b / (16 / RB), r = (b % (16 / RB)) * RB + q;
-        return wr + m * 32 + (r / 4) * 8 + (lane / 32) * 4 + (r % 4);
-    };
-    struct Batch {
-        uint32_t nij[RB][WN], nik[RB][WN];
-        int4 ri[RB];
-    };
-    auto load_batch = [&](int b, Batch& o) {
-#pragma unroll
-        for (int q = 0; q < RB; ++q) {
-            const int4 ri = rowi[row_dk(b, q)];
-            o.ri[q] = ri;
-#pragma unroll
-            for (int nn = 0; nn < WN; ++nn) {
-                o.nij[q][nn] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                    rn2, (int)(((uint32_t)ri.x + (uint32_t)ii[nn]) * 4), 0, 0);
-                o.nik[q][nn] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                    rn2, (int)(((uint32_t)ri.y + (uint32_t)ii[nn]) * 4), 0, 0);
-            }
-        }
-    };
-    auto store_batch = [&](int b, const Batch& o) {
-        const int m = b / (16 / RB);
-#pragma unroll
-        for (int q = 0; q < RB; ++q) {
-            const int r = (b % (16 / RB)) * RB + q;
-            const int dk = row_dk(b, q);
-            const R rr = rs2[dk];
-            const uint32_t njk = (uint32_t)rnj[dk];
-            const int4 ri = o.ri[q];
-#pragma unroll
-            for (int nn = 0; nn < WN; ++nn) {
-                const bool ok = ii[nn] < ri.z;
-                const uint32_t n3 = o.nij[q][nn] + o.nik[q][nn] + njk - (uint32_t)acc[m][nn][r];
-                const R d = ls[nn] + rr;
-                const R dd = d > (R)0 ? d : (R)1;
-                float qv;
-                if constexpr (F32)
-                    qv = div_u24((float)(3u * n3), dd);
-                else
-                    qv = (float)((3.0 * (double)n3) / dd);
-                const float c = d > (R)0 ? qv : 0.0f;
-                const uint32_t off =
-                    ok ? ((uint32_t)ri.w + (uint32_t)ii[nn]) * 4u : 0x80000000u;
-                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, c), rc3,
-                                                      (int)off, 0, 0);
-            }
-        }
-    };
-    Batch bt[2];
-    load_batch(0, bt[0]);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        if (b + 1 < NB) load_batch(b + 1, bt[(b + 1) & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-        store_batch(b, bt[b & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
 // Half h of tile t of part PART of the split tiling: part 0's output columns
 // (pairs) 128 h .. 128 h + 127, part 1's output rows (pairs) likewise; four
 // waves of 128 x 64, two workgroups per CU (the epilogue and barriers of
@@ -1429,37 +1123,6 @@ static bool lv_aligned(const MfmaLaunch& m) {
     return (uintptr_t)m.V % 16 == 0 && m.ld % 16 == 0;
 }
 
-// 2-way half tiles with LDS-direct staging (rows 16-byte aligned, n_f a
-// multiple of kLvdMK): stages of kLvdMK fields of the tile's 384 rows (256 j
-// rows, then 128 i rows) go from global memory straight into a ring of
-// kLvdStages LDS slots (global_load_lds_dwordx4: one wave instruction fills
-// 1 KB, 16 rows of 64 bytes, lane l at byte 16 l), two stages ahead of the
-// multiply-adds, so no registers hold staged data and the fragment reads of
-// the next k-step are in flight while a k-step runs.  16-byte chunk c of
-// row r sits at chunk position c ^ lvd_swz(r).  Rows past n_v load row
-// n_v - 1 (their outputs are never stored).  One barrier per stage.
-constexpr int kLvdMK = 64;
-constexpr int kLvdStages = 3;
-
-// Chunk swizzle of 64-byte rows: for every chunk c, the slots of any 8
-// consecutive rows are distinct modulo 128 bytes and those of any 16
-// consecutive rows distinct modulo 256 bytes (b128 fragment reads free of
-// bank conflicts whether the LDS serves 8 or 16 lanes at once); rows r and
-// r + 32 share a swizzle.
-__device__ __forceinline__ int lvd_swz(int r) { return ((r >> 1) ^ (r >> 3)) & 3; }
-
-// This wave's stage loads but the N most recent have landed and its LDS
-// accesses are done, then the barrier; the empty asm statements keep the
-// compiler from moving memory accesses across.
-template <int N>
-__device__ __forceinline__ void lvd_sync() {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 15) | (0x7 << 4) | ((N >> 4) << 14));   // lgkmcnt 0
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 // One kLvdMK-field stage of a wave's 128 x 64 block: A rows wr + 0..127 and
 // B rows wc + 0..63 of LDS regions of 64-byte rows in the lvd_swz layout
 // (wr, wc multiples of 32); the fragments of the second k-step are read
@@ -1527,6 +1190,15 @@ __device__ __forceinline__ void lvd_stage(const int8_t* A, const int8_t* B, int 
     }
 }
 
+// 2-way half tiles with LDS-direct staging (rows 16-byte aligned, n_f a
+// multiple of kLvdMK): stages of kLvdMK fields of the tile's 384 rows (256 j
+// rows, then 128 i rows) go from global memory straight into a ring of
+// kLvdStages LDS slots (global_load_lds_dwordx4: one wave instruction fills
+// 1 KB, 16 rows of 64 bytes, lane l at byte 16 l), two stages ahead of the
+// multiply-adds, so no registers hold staged data and the fragment reads of
+// the next k-step are in flight while a k-step runs.  16-byte chunk c of
+// row r sits at chunk position c ^ lvd_swz(r).  Rows past n_v load row
+// n_v - 1 (their outputs are never stored).  One barrier per stage.
 template <int LC, int MODE>
 __global__ __launch_bounds__(256, 2) void ps_mfma2_lvd_kernel(LvArgs a) {
     constexpr int MK = kLvdMK;
@@ -1968,180 +1640,24 @@ static hipError_t go_lv(const MfmaLaunch& m, hipStream_t st) {
     return lv_aligned(m) ? go_lv_al<WAY, true>(m, st) : go_lv_al<WAY, false>(m, st);
 }
 
-// ---------------------------------------------------------------------------
-// LDS-direct variant (used for fp4): field tiles go from global memory
-// straight into LDS (global_load_lds_dwordx4: one wave instruction fills
-// 1 KB of LDS, lane l at byte 16 l), so no registers hold staged data and
-// the 128-byte tile fits the fp4 kernel without spills.  Two buffers: tile
-// kt+1 loads while tile kt is consumed.  Rows are kDmaMK bytes, unpadded;
-// 16-byte chunk c of row r sits at chunk position c ^ dma_swz(r).  Rows past
-// n_v load row n_v - 1 (their outputs are never stored).
-// Measured on the int8 planes the register-staged kernel above is faster
-// (it is kept for int8 planes); on fp4 this one is.  (The fused int8 level
-// tiles have an LDS-direct form of their own, ps_mfma2_lvd_kernel.)
-// ---------------------------------------------------------------------------
-constexpr int kDmaMK = 128;
-
-// Chunk swizzle of row r: for every chunk c, the 16-byte slots of any 8
-// consecutive rows are distinct modulo 128 bytes and those of any 16
-// consecutive rows distinct modulo 256 bytes, so fragment reads are free of
-// bank conflicts whether the LDS serves 8 or 16 lanes of a b128 read at once.
-// Rows r and r + 32 share a swizzle.
-__device__ __forceinline__ int dma_swz(int r) { return (r % 8) ^ ((r / 8) % 2); }
-
-// Tile hand-over between the waves of a workgroup: this wave's LDS reads are
-// done and all of its tile loads have landed, then the barrier.  The empty
-// asm statements keep the compiler from moving memory accesses across.
-__device__ __forceinline__ void tile_sync() {
-    // vmcnt 0, expcnt unconstrained (7), lgkmcnt 0
-    __builtin_amdgcn_s_waitcnt(0x7 << 4);
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-template <int FMT, int WN>
-__global__ __launch_bounds__(mfma_threads<WN>(), 1) void ps_mfma2_dma_kernel(MfmaArgs a) {
-    constexpr int MK = kDmaMK;
-    constexpr int kWaves = mfma_threads<WN>() / 64;
-    constexpr int R = MK / 16;                 // chunks per row
-    constexpr int RB = 1024 / MK;              // rows per wave instruction
-    constexpr int NBW = kMB / RB / kWaves;     // instructions per wave per operand per tile
-    constexpr int kStageBytes = kMB * MK;
-    static_assert(NBW >= 1 && kMB % (RB * kWaves) == 0, "stage split");
-    using AccT = typename std::conditional<FMT == kFmtF4, v16f_t, v16i_t>::type;
-    __shared__ __attribute__((aligned(1024))) int8_t As[2 * kStageBytes];   // j rows
-    __shared__ __attribute__((aligned(1024))) int8_t Bs[2 * kStageBytes];   // i rows
-    const int64_t t = a.item0 + (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) +
-                      blockIdx.x / kXcds;
-    if (t >= a.ntiles) return;
-    int64_t bi, bj;
-    grouped_tri_decode<kGroup>(t, a.nb, bi, bj);
-    const int64_t i0 = bi * kMB, j0 = bj * kMB;
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int wr = (wave % 2) * 128;
-    const int wc = (wave / 2) * 32 * WN;
-    const bool active = (i0 + wc < a.n_v) && (j0 + wr < a.n_v) && (i0 + wc + 1 < j0 + wr + 128);
-
-    AccT acc[4][WN];
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int n = 0; n < WN; ++n) acc[m][n] = (AccT){};
-
-    // per-lane source rows and chunk offsets of this wave's loads
-    const int8_t* srcA[NBW];
-    const int8_t* srcB[NBW];
-#pragma unroll
-    for (int u = 0; u < NBW; ++u) {
-        const int row = (wave + kWaves * u) * RB + lane / R;
-        const int c = (lane % R) ^ dma_swz(row);
-        const int64_t gj = j0 + row < a.n_v ? j0 + row : a.n_v - 1;
-        const int64_t gi = i0 + row < a.n_v ? i0 + row : a.n_v - 1;
-        srcA[u] = a.P + gj * a.kp + c * 16;
-        srcB[u] = a.P + gi * a.kp + c * 16;
-    }
-    auto issue = [&](int64_t kt, int buf) {
-        const int64_t k0 = kt * MK;
-#pragma unroll
-        for (int u = 0; u < NBW; ++u) {
-            const int blk = (wave + kWaves * u) * 1024;
-            __builtin_amdgcn_global_load_lds((const void*)(srcA[u] + k0),
-                                             (void*)(As + buf * kStageBytes + blk), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((const void*)(srcB[u] + k0),
-                                             (void*)(Bs + buf * kStageBytes + blk), 16, 0, 0);
-        }
-    };
-
-    const int64_t nk = a.kp / MK;
-    issue(0, 0);
-    const int fr = lane % 32, hk = lane / 32;
-    const int sw = dma_swz(fr);   // swizzle of rows wr + m*32 + fr and wc + n*32 + fr
-    if (active) {
-        for (int64_t kt = 0; kt < nk; ++kt) {
-            const int cur = (int)(kt & 1);
-            tile_sync();   // tile kt in LDS everywhere; tile kt-1 no longer read
-            if (kt + 1 < nk) issue(kt + 1, cur ^ 1);
-            const int8_t* A = As + cur * kStageBytes;
-            const int8_t* B = Bs + cur * kStageBytes;
-            // fragments of k-step ks+1 are read into the other register set
-            // while k-step ks runs (scheduled below; measured 4% faster)
-            v4i_t fa[2][4], fb[2][WN];
-            auto frag = [&](int ks, int sl) {
-                const int co = ((ks * 2 + hk) ^ sw) * 16;
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    fa[sl][m] = *(const v4i_t*)(A + (wr + m * 32 + fr) * MK + co);
-#pragma unroll
-                for (int n = 0; n < WN; ++n)
-                    fb[sl][n] = *(const v4i_t*)(B + (wc + n * 32 + fr) * MK + co);
-            };
-            frag(0, 0);
-#pragma unroll
-            for (int ks = 0; ks < MK / 32; ++ks) {
-                if (ks + 1 < MK / 32) frag(ks + 1, (ks + 1) & 1);
-                const int sl = ks & 1;
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-#pragma unroll
-                    for (int n = 0; n < WN; ++n) {
-                        if constexpr (FMT == kFmtI8) {
-                            acc[m][n] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                                fa[sl][m], fb[sl][n], acc[m][n], 0, 0, 0);
-                        } else {
-                            const v8i_t xa = {fa[sl][m].x, fa[sl][m].y, fa[sl][m].z,
-                                              fa[sl][m].w, 0, 0, 0, 0};
-                            const v8i_t xb = {fb[sl][n].x, fb[sl][n].y, fb[sl][n].z,
-                                              fb[sl][n].w, 0, 0, 0, 0};
-                            acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                                xa, xb, acc[m][n], 4, 4, 0, 127, 0, 127);
-                        }
-                    }
-            }
-            if constexpr (WN == 2) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-#pragma unroll
-                for (int ks = 0; ks < MK / 32 - 1; ++ks) {
-#pragma unroll
-                    for (int i = 0; i < 6; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                    }
-                    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                }
-                __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-            }
-        }
-    } else {
-        for (int64_t kt = 0; kt < nk; ++kt) {
-            tile_sync();
-            if (kt + 1 < nk) issue(kt + 1, (int)(kt & 1) ^ 1);
-        }
-        return;   // the last tile_sync waited for every load of this wave
-    }
-
-    mfma_epilogue<WN>(acc, a, i0, j0, wr, wc, lane);
-}
-
 // Thermometer planes of V into m.planes (when m.expand); returns the plane-row
 // length in bytes through kp.
-template <int FMT>
 static hipError_t expand_planes(const MfmaLaunch& m, int64_t& kp, hipStream_t st) {
-    const int64_t kpad = plane_fields(m.n_f, FMT);
-    kp = (int64_t)m.levels * kpad / fields_per_byte(FMT);
+    const int64_t kpad = plane_fields(m.n_f);
+    kp = (int64_t)m.levels * kpad;
     if (!m.expand) return hipSuccess;
     const int64_t total = m.n_v * (kpad / 32);
     int64_t blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(ps_thermo_expand_kernel<FMT>, dim3((unsigned)blocks), dim3(256), 0, st,
+    hipLaunchKernelGGL(ps_thermo_expand_kernel, dim3((unsigned)blocks), dim3(256), 0, st,
                        (const uint8_t*)m.V, m.n_f, m.n_v, m.ld, m.levels, kpad, m.planes);
     return hipGetLastError();
 }
 
-template <int FMT, int WN>
+template <int WN>
 static hipError_t go_mfma2(const MfmaLaunch& m, hipStream_t st) {
     int64_t kp = 0;
-    hipError_t e = expand_planes<FMT>(m, kp, st);
+    hipError_t e = expand_planes(m, kp, st);
     if (e != hipSuccess) return e;
     const int64_t nb = (m.n_v + kMB - 1) / kMB;
     const int64_t T = nb * (nb + 1) / 2;
@@ -2149,19 +1665,13 @@ static hipError_t go_mfma2(const MfmaLaunch& m, hipStream_t st) {
     return launch_items(T, mfma_threads<WN>(), kXcds, [&](unsigned grid, int64_t item0) {
         MfmaArgs b = a;
         b.item0 = item0;
-        if constexpr (FMT == kFmtF4 && WN == 2)
-            hipLaunchKernelGGL((ps_mfma2_dma_kernel<FMT, WN>), dim3(grid),
-                               dim3(mfma_threads<WN>()), 0, st, b);
-        else
-            hipLaunchKernelGGL((ps_mfma2_kernel<FMT, WN>), dim3(grid), dim3(mfma_threads<WN>()),
-                               0, st, b);
+        hipLaunchKernelGGL(ps_mfma2_kernel<WN>, dim3(grid), dim3(mfma_threads<WN>()), 0, st, b);
     });
 }
 
-template <int FMT>
 static hipError_t go_mfma3(const MfmaLaunch& m, hipStream_t st) {
     int64_t kp = 0;
-    hipError_t e = expand_planes<FMT>(m, kp, st);
+    hipError_t e = expand_planes(m, kp, st);
     if (e != hipSuccess) return e;
     // whole 256-wide tiles of each slab rectangle, then 128-wide edge tiles
     constexpr int kEdge = kMB / 2;
@@ -2177,7 +1687,7 @@ static hipError_t go_mfma3(const MfmaLaunch& m, hipStream_t st) {
         e = launch_items(T1, mfma_threads<2>(), kXcds, [&](unsigned grid, int64_t item0) {
             MfmaArgs b = a;
             b.item0 = item0;
-            hipLaunchKernelGGL((ps_mfma3_kernel<FMT, kMB>), dim3(grid), dim3(mfma_threads<2>()),
+            hipLaunchKernelGGL(ps_mfma3_kernel<kMB>, dim3(grid), dim3(mfma_threads<2>()),
                                0, st, b);
         });
     if (e != hipSuccess || T2 == 0) return e;
@@ -2187,23 +1697,22 @@ static hipError_t go_mfma3(const MfmaLaunch& m, hipStream_t st) {
     return launch_items(T2, mfma_threads<2, kEdge>(), kXcds, [&](unsigned grid, int64_t item0) {
         MfmaArgs b = a;
         b.item0 = item0;
-        hipLaunchKernelGGL((ps_mfma3_kernel<FMT, kEdge>), dim3(grid),
+        hipLaunchKernelGGL(ps_mfma3_kernel<kEdge>, dim3(grid),
                            dim3(mfma_threads<2, kEdge>()), 0, st, b);
     });
 }
 
 hipError_t launch_mfma3(const MfmaLaunch& m, hipStream_t st) {
     if (m.n_v < 3 || m.j_end <= m.j_begin) return hipSuccess;
-    if (mfma_fused(m.n_f, m.levels, m.fmt, 0)) return go_lv<3>(m, st);
-    return m.fmt == kFmtF4 ? go_mfma3<kFmtF4>(m, st) : go_mfma3<kFmtI8>(m, st);
+    if (mfma_fused(m.n_f, m.levels, 0, 0)) return go_lv<3>(m, st);
+    return go_mfma3(m, st);
 }
 
 hipError_t launch_mfma2(const MfmaLaunch& m, hipStream_t st) {
     if (m.n_v < 2) return hipSuccess;
-    if (mfma_fused(m.n_f, m.levels, m.fmt, m.wide)) return go_lv<2>(m, st);
-    if (m.wide)
-        return m.fmt == kFmtF4 ? go_mfma2<kFmtF4, 4>(m, st) : go_mfma2<kFmtI8, 4>(m, st);
-    return m.fmt == kFmtF4 ? go_mfma2<kFmtF4, 2>(m, st) : go_mfma2<kFmtI8, 2>(m, st);
+    if (mfma_fused(m.n_f, m.levels, 0, m.wide)) return go_lv<2>(m, st);
+    if (m.wide) return go_mfma2<4>(m, st);
+    return go_mfma2<2>(m, st);
 }
 
 }  // namespace ps

@@ -122,11 +122,14 @@ bool is_mfma(int path) { return path == PS_PATH_MFMA || path == PS_PATH_MFMA_FP4
 static bool mfma_can(int path, int way, int64_t n_f, int64_t n_v, int levels, int wide,
                      int64_t ld) {
     if (path == PS_PATH_MFMA_FP4)
-        return (int64_t)levels * n_f < ((int64_t)1 << 24) && mfma_row_fits(n_f, levels, 1);
+        return bp_exact(n_f, levels) && mfma_row_fits(n_f, levels, 1);
     if (mfma_fused(n_f, levels, 0, wide))
         return mfma_ld_fits(ld) && (way != 3 || mfma3_nv_fits(n_v));
     return (int64_t)levels * n_f < ((int64_t)1 << 31) && mfma_row_fits(n_f, levels, 0);
 }
+
+// AUTO keeps triangles of up to this many vectors on the paths without a plane workspace.
+static constexpr int64_t kBpMinVectors = 1024;
 
 // A tuned entry for (dt, way, path) covering the shape, or -1.
 static int tuned(int32_t dt, int way, int32_t path, int64_t n_f, int64_t n_v) {
@@ -149,8 +152,19 @@ int choose_path(int32_t dt, const ps_opts* o, int way, int64_t n_f, int64_t n_v,
     if ((t == PS_PATH_MFMA || t == PS_PATH_MFMA_FP4) &&
         mfma_can(t, way, n_f, n_v, o->levels, wide, ld))
         return t;
+    if (mfma_can(PS_PATH_MFMA_FP4, way, n_f, n_v, o->levels, wide, ld) &&
+        (way == 2 ? n_v > kBpMinVectors : bp3_fits(n_f, n_v, o->levels)))
+        return PS_PATH_MFMA_FP4;
     return mfma_can(PS_PATH_MFMA, way, n_f, n_v, o->levels, wide, ld) ? PS_PATH_MFMA
                                                                       : PS_PATH_VALU;
+}
+
+int path_without_planes(int32_t dt, const ps_opts* o, int64_t n_f, int64_t n_v, int64_t ld) {
+    const int levels = o ? o->levels : 0;
+    return dt == PS_U8 && mfma_fused(n_f, levels, 0, 0) &&
+                   mfma_can(PS_PATH_MFMA, 3, n_f, n_v, levels, 0, ld)
+               ? PS_PATH_MFMA
+               : PS_PATH_VALU;
 }
 
 int mfma_group(int64_t n_f, int64_t n_v) {

@@ -276,6 +276,16 @@ static ps_status ps2_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
         return fail(PS_ERR_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, need);
     if (!aligned(workspace, 256)) return fail(PS_ERR_ARG, "workspace is not 256-byte aligned");
     hipError_t e;
+    // planes of bits: the FP4 path, and binary data unless the call names a
+    // tile configuration or a shard of one (those are the VALU tiles)
+    if (path == PS_PATH_MFMA_FP4 ||
+        (bits && nshards == 1 && opts->tile == 0 && bp_exact(n_f, 1))) {
+        e = launch_bp_pack((const uint8_t*)V, n_f, n_v, ld, levels, (uint32_t*)planes,
+                           s ? nullptr : s_ws, stream);
+        BpLaunch b{n_f, n_v, levels, (const uint32_t*)planes, s ? s : s_ws, c2, (int32_t*)n2};
+        if (e == hipSuccess) e = launch_bp2(b, stream);
+        return e == hipSuccess ? PS_OK : hip_fail(e, "2-way bit planes launch");
+    }
     if (!s) {
         e = launch_sums(V, dtype, n_f, n_v, ld, s_ws, nullptr, stream);
         if (e != hipSuccess) return hip_fail(e, "sums launch");
@@ -283,7 +293,7 @@ static ps_status ps2_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
     }
     if (is_mfma(path)) {
         // opts.tile: 0 or 1 -> 4x2 blocks per wave, 2 -> 4x4 blocks per wave
-        MfmaLaunch m{V,    n_f,  n_v, ld, levels, s, c2, n2, planes, path == PS_PATH_MFMA_FP4 ? 1 : 0,
+        MfmaLaunch m{V,    n_f,  n_v, ld, levels, s, c2, n2, planes,
                      wide, mfma_group(n_f, n_v), 1, 0, 0, nullptr, nullptr};
         e = launch_mfma2(m, stream);
         if (e == hipErrorNotSupported)
@@ -344,14 +354,46 @@ static size_t ws3_layout(int64_t n_v, int64_t npre, int32_t s_given, int32_t n2_
     return c.used;
 }
 
-// 3-way on the matrix cores (uint8 levels): planes once, the pair
+// 3-way on planes of bits (bitplane.hip; bp3_fits): packing and sums in one
+// pass, the pair numerators (unless given), the slices with Eq. 1.
+// planes_bytes: the workspace region of the planes.
+static ps_status ps3_bp(const void* V, int64_t n_f, int64_t n_v, int64_t ld, const double* s,
+                        const void* n2, int64_t j_begin, int64_t j_end, float* c3,
+                        void* workspace, size_t ws_bytes, int levels, size_t planes_bytes,
+                        hipStream_t stream) {
+    double* s_ws = nullptr;
+    void* n2_ws = nullptr;
+    int64_t* prefix = nullptr;
+    uint32_t* planes = nullptr;
+    const size_t need =
+        ws3_layout(n_v, prefix3_entries(n_v, j_begin, j_end), s != nullptr, n2 != nullptr, 4, 1, 1,
+                   ps3_stage_size(n_v, j_begin, j_end), planes_bytes, workspace, &s_ws, &n2_ws,
+                   &prefix, nullptr, &planes);
+    if (ws_bytes < need || !workspace)
+        return fail(PS_ERR_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, need);
+    if (!aligned(workspace, 256)) return fail(PS_ERR_ARG, "workspace is not 256-byte aligned");
+    hipError_t e = launch_bp_pack((const uint8_t*)V, n_f, n_v, ld, levels, planes,
+                                  s ? nullptr : s_ws, stream);
+    if (e != hipSuccess) return hip_fail(e, "bit packing launch");
+    BpLaunch b{n_f, n_v, levels, planes, s ? s : s_ws, nullptr, (int32_t*)n2_ws,
+               j_begin, j_end, prefix, c3};
+    if (!n2) {
+        e = launch_bp2(b, stream);
+        if (e != hipSuccess) return hip_fail(e, "3-way numerator prepass launch");
+    } else {
+        b.n2 = (int32_t*)n2;
+    }
+    e = launch_bp3(b, stream);
+    return e == hipSuccess ? PS_OK : hip_fail(e, "3-way bit planes launch");
+}
+
+// 3-way on the int8 matrix cores (uint8 levels): planes once, the pair
 // numerators by the 2-way MFMA kernel (unless given), the masked slices, then
 // Eq. 1 from exact integers.
 static ps_status ps3_mfma(const void* V, int64_t n_f, int64_t n_v, int64_t ld, const double* s,
                           const void* n2, int64_t j_begin, int64_t j_end, float* c3,
-                          void* workspace, size_t ws_bytes, int path, int levels, int tile,
+                          void* workspace, size_t ws_bytes, int levels, int tile,
                           hipStream_t stream) {
-    const int fmt = path == PS_PATH_MFMA_FP4 ? 1 : 0;
     const int64_t stage = ps3_stage_size(n_v, j_begin, j_end);
     double* s_ws = nullptr;
     void* n2_ws = nullptr;
@@ -360,7 +402,7 @@ static ps_status ps3_mfma(const void* V, int64_t n_f, int64_t n_v, int64_t ld, c
     uint32_t* planes = nullptr;
     const size_t need = ws3_layout(n_v, prefix3_entries(n_v, j_begin, j_end), s != nullptr,
                                    n2 != nullptr, 4, 1, 1, stage,
-                                   mfma_workspace_bytes(n_f, n_v, levels, fmt, 0), workspace,
+                                   mfma_workspace_bytes(n_f, n_v, levels, 0, 0), workspace,
                                    &s_ws, &n2_ws, &prefix, &partial, &planes);
     if (ws_bytes < need || !workspace)
         return fail(PS_ERR_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, need);
@@ -371,7 +413,7 @@ static ps_status ps3_mfma(const void* V, int64_t n_f, int64_t n_v, int64_t ld, c
         if (e != hipSuccess) return hip_fail(e, "sums launch");
         s = s_ws;
     }
-    MfmaLaunch m{V,   n_f, n_v, ld, levels, s, nullptr, nullptr, (int8_t*)planes, fmt, 0,
+    MfmaLaunch m{V,   n_f, n_v, ld, levels, s, nullptr, nullptr, (int8_t*)planes, 0,
                  mfma_group(n_f, n_v), 1, j_begin, j_end, prefix, c3, prefix + (n_v + 1)};
     if (!n2) {   // pair numerators; this launch also writes the planes
         MfmaLaunch m2 = m;
@@ -385,7 +427,7 @@ static ps_status ps3_mfma(const void* V, int64_t n_f, int64_t n_v, int64_t ld, c
     m.slab3 = tile == 2;
     e = launch_mfma3(m, stream);
     if (e != hipSuccess) return hip_fail(e, "3-way mfma launch");
-    if (mfma_fused(n_f, levels, fmt, 0)) return PS_OK;   // Eq. 1 applied in the slices
+    if (mfma_fused(n_f, levels, 0, 0)) return PS_OK;   // Eq. 1 applied in the slices
     Mg3Launch f{V, n_f, n_v, ld, s, n2, j_begin, j_end, c3, prefix, 0, 0, 1, 0, nullptr, kSlabAll};
     e = launch_c3_finish_int(f, stream);
     return e == hipSuccess ? PS_OK : hip_fail(e, "3-way finish launch");
@@ -524,6 +566,13 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
     if (from_scratch) {
         const size_t need = ps3_workspace_size(dtype, n_f, n_v, s != nullptr, n2 != nullptr,
                                                j_begin, j_end, opts);
+        // AUTO's planes may not fit where the int8 path, which has none, does
+        if (need > ws_bytes && path == PS_PATH_MFMA_FP4 && opts->path == PS_PATH_AUTO) {
+            ps_opts o = *opts;
+            o.path = path_without_planes(dtype, opts, n_f, n_v, ld);
+            return ps3_run(V, dtype, n_f, n_v, ld, s, n2, j_begin, j_end, c3, workspace, ws_bytes,
+                           true, &o, stream);
+        }
         if (need > ws_bytes)
             return fail(PS_ERR_WORKSPACE,
                         "ps3_compute_noalloc: this call needs %zu bytes of scratch, the static "
@@ -535,9 +584,19 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
     void* n2_ws = nullptr;
     int64_t* prefix = nullptr;
     float* partial = nullptr;
-    if (is_mfma(path)) return ps3_mfma(V, n_f, n_v, ld, s, n2, j_begin, j_end, c3, workspace,
-                                       ws_bytes, path, levels, opts ? opts->tile : 0, stream);
     const bool bits = is_bits(opts);
+    // planes of bits: the FP4 path, and binary data unless the call names a
+    // tile configuration (those are the VALU tiles)
+    if ((path == PS_PATH_MFMA_FP4 || (bits && opts->tile == 0)) && bp3_fits(n_f, n_v, levels))
+        return ps3_bp(V, n_f, n_v, ld, s, n2, j_begin, j_end, c3, workspace, ws_bytes, levels,
+                      bits ? bits_bytes(n_f, n_v) : mfma_workspace_bytes(n_f, n_v, levels, 1, 0),
+                      stream);
+    // stages of more vectors than the planes' 32-bit offsets allow: the same sums on
+    // another path (its workspace is no larger)
+    const int run = path == PS_PATH_MFMA_FP4 ? path_without_planes(dtype, opts, n_f, n_v, ld) : path;
+    if (run == PS_PATH_MFMA)
+        return ps3_mfma(V, n_f, n_v, ld, s, n2, j_begin, j_end, c3, workspace, ws_bytes, levels,
+                        path == run ? opts->tile : 0, stream);
     const int32_t kdt = bits ? PS_B1 : dtype;   // operand type of the kernels
     const int cfg2 = choose_cfg(kdt, 2, bits ? PS_PATH_BITS : PS_PATH_VALU, n_f, n_v, opts);
     const Split sp2 = bits ? Split{1, 0} : plan_split(dtype, n_f, n_v, cfg2, opts);

@@ -274,10 +274,15 @@ Split plan_split(int32_t dt, int64_t n_f, int64_t n_v, int cfg, const ps_opts* o
 bool is_mfma(int path);
 // AUTO for PS_U8 data with 1 <= levels <= 15: the path a tuned entry
 // (dtype, way, PS_PATH_AUTO) registers for the shape, when that path can
-// take it; else the int8 MFMA path when its rows fit the 32-bit tile offsets
+// take it; else the FP4 path (planes of bits) for triangles of more than
+// kBpMinVectors vectors and for the 3-way slices when it can take the shape;
+// else the int8 MFMA path when its rows fit the 32-bit tile offsets
 // (mfma_ld_fits on the fused path, mfma_row_fits on planes); else VALU.  ld
 // is the row stride (n_f in size queries).
 int choose_path(int32_t dt, const ps_opts* o, int way, int64_t n_f, int64_t n_v, int64_t ld);
+// The 3-way path AUTO takes for levels 1..15 where the FP4 path's planes have no room:
+// int8 MFMA when it can take the shape, else VALU.
+int path_without_planes(int32_t dt, const ps_opts* o, int64_t n_f, int64_t n_v, int64_t ld);
 // Tile order of the fused 2-way int8 MFMA kernel: block columns are walked in
 // groups of mfma_group(...) columns (a tuned entry for path MFMA registers
 // idx, the group being 2^idx; default 4).
@@ -414,7 +419,7 @@ hipError_t launch_put(void* dst, const void* src, size_t bytes, hipStream_t st);
 hipError_t launch_batch_expand(const BatchGroup* groups, int32_t ngroups, BatchTile* tiles,
                                int64_t ntiles, hipStream_t st);
 
-// Thermometer int8 MFMA path (PS_U8).
+// Thermometer int8 MFMA path (PS_U8; path FP4: BpLaunch).
 struct MfmaLaunch {
     const void* V;
     int64_t n_f, n_v, ld;
@@ -423,7 +428,6 @@ struct MfmaLaunch {
     float* c2;
     void* n2;
     int8_t* planes;              // workspace: mfma_workspace_bytes()
-    int fmt;                     // 0: int8 planes, 1: fp4 (e2m1) planes
     int wide;                    // 0: 4x2 MFMA blocks per wave, 1: 4x4
     int group;                   // fused 2-way: block columns per tile-order group
     int expand;                  // 1: write the planes first; 0: planes already hold V's
@@ -469,7 +473,8 @@ inline int64_t split3(int64_t n_v, int64_t jb, int64_t je) {
 }
 // Plane workspace of a thermometer launch (0 on the fused path).
 size_t mfma_workspace_bytes(int64_t n_f, int64_t n_v, int levels, int fmt, int wide);
-// Bytes of one thermometer plane row (all levels) of an n_f-field vector.
+// Bytes of one thermometer plane row (all levels) of an n_f-field vector; fmt 0:
+// int8 planes, 1: what the FP4 path reserves.
 int64_t mfma_row_bytes(int64_t n_f, int levels, int fmt);
 hipError_t launch_mfma2(const MfmaLaunch& a, hipStream_t st);
 // Output tile edge of the MFMA kernels (the 3-way prefix is over these tiles).
@@ -497,6 +502,33 @@ int64_t flat_tiles(int64_t n_v, int64_t jb, int64_t je, int bm);
 // Total tiles of the lex-ordered tiling (lex_row_tiles, lex_col_tiles), and
 // the prefix of its column-tile counts (launch_prefix3_flat with lex).
 int64_t lex_tiles(int64_t n_v, int64_t jb, int64_t je, int bm);
+
+// Bit planes on the fp4 matrix cores (bitplane.hip): levels * n_f < 2^24.
+struct BpLaunch {
+    int64_t n_f, n_v;
+    int levels;
+    const uint32_t* planes;      // n_v rows of bp_row_words(n_f, levels) words
+    const double* s;
+    float* c2;                   // 2-way: may be null
+    int32_t* n2;                 // 2-way output (may be null); 3-way: the pair numerators
+    int64_t j_begin, j_end;      // 3-way
+    int64_t* prefix;
+    float* c3;
+};
+int64_t bp_row_words(int64_t n_f, int levels);
+// Whether the bit planes hold the shape: sums exact in FP32, and for the 3-way
+// slices all planes and the whole pair table within 32-bit byte offsets.
+inline bool bp_exact(int64_t n_f, int levels) {
+    return (int64_t)levels * n_f < ((int64_t)1 << 24);
+}
+inline bool bp3_fits(int64_t n_f, int64_t n_v, int levels) {
+    return bp_exact(n_f, levels) && mfma3_split_ok(n_v, bp_row_words(n_f, levels) * 4);
+}
+// V -> planes; with s, also the per-vector sums.
+hipError_t launch_bp_pack(const uint8_t* V, int64_t n_f, int64_t n_v, int64_t ld, int levels,
+                          uint32_t* planes, double* s, hipStream_t st);
+hipError_t launch_bp2(const BpLaunch& b, hipStream_t st);
+hipError_t launch_bp3(const BpLaunch& b, hipStream_t st);
 // Output reduction (reduce.hip).
 hipError_t launch_quantize_u8(const float* c, int64_t n, uint8_t* q, hipStream_t st);
 int64_t select_tiles(int64_t n);
