@@ -5,85 +5,9 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "mgemm_core.h"
+#include "sums.h"
 
 namespace ps {
-
-// ---------------------------------------------------------------------------
-// Per-vector sums s_i = sum_q v_{i,q} in FP64 (exact integers for PS_U8),
-// plus the count of entries outside the domain v >= 0 (negative, NaN, Inf).
-// One wave per vector; 16-byte coalesced loads along the fields.
-// ---------------------------------------------------------------------------
-template <int DT>
-__device__ __forceinline__ void sum_word(uint32_t w, double& acc, uint64_t& iacc, int& bad) {
-    if constexpr (DT == PS_F32) {
-        acc += (double)as_f32(w);
-        bad += ((w & 0x7f800000u) == 0x7f800000u) | ((w >> 31) & (w != 0x80000000u));
-    } else if constexpr (DT == PS_F16) {
-        const h2_t h = as_h2(w);
-        acc += (double)(float)h.x;
-        acc += (double)(float)h.y;
-        const uint32_t lo = w & 0xffffu, hi = w >> 16;
-        bad += ((lo & 0x7c00u) == 0x7c00u) | ((lo >> 15) & (lo != 0x8000u));
-        bad += ((hi & 0x7c00u) == 0x7c00u) | ((hi >> 15) & (hi != 0x8000u));
-    } else {
-        iacc += (w & 0xffu) + ((w >> 8) & 0xffu) + ((w >> 16) & 0xffu) + (w >> 24);
-    }
-}
-
-// One FP64 element: its value and whether it is outside v >= 0 (negative
-// other than -0, NaN or Inf).
-__device__ __forceinline__ void sum_f64(uint64_t x, double& acc, int& bad) {
-    acc += __builtin_bit_cast(double, x);
-    bad += ((x & 0x7ff0000000000000ull) == 0x7ff0000000000000ull) |
-           (int)((x >> 63) & (x != 0x8000000000000000ull));
-}
-
-template <int DT>
-__device__ __forceinline__ void sum_row(const char* row, int64_t n_f, bool vec,
-                                        double& acc, uint64_t& iacc, int& bad) {
-    constexpr int ESZ = Ops<DT>::kEsz;
-    const int lane = threadIdx.x % 64;
-    const int64_t nbytes = n_f * ESZ;
-    int64_t done = 0;
-    if (vec) {
-        const int64_t full = nbytes / 16 * 16;
-        for (int64_t b = (int64_t)lane * 16; b < full; b += 64 * 16) {
-            const uint4 v = *(const uint4*)(row + b);
-            if constexpr (DT == PS_F64) {
-                sum_f64(((uint64_t)v.y << 32) | v.x, acc, bad);
-                sum_f64(((uint64_t)v.w << 32) | v.z, acc, bad);
-            } else {
-                sum_word<DT>(v.x, acc, iacc, bad);
-                sum_word<DT>(v.y, acc, iacc, bad);
-                sum_word<DT>(v.z, acc, iacc, bad);
-                sum_word<DT>(v.w, acc, iacc, bad);
-            }
-        }
-        done = full / ESZ;
-    }
-    if constexpr (DT == PS_F64) {   // whole 8-byte elements
-        for (int64_t q = done + lane; q < n_f; q += 64)
-            sum_f64(*(const uint64_t*)(row + 8 * q), acc, bad);
-    } else {
-        for (int64_t q = done + lane; q < n_f; q += 64) {
-            uint32_t w;
-            if (ESZ == 4) w = *(const uint32_t*)(row + 4 * q);
-            else if (ESZ == 2) w = *(const unsigned short*)(row + 2 * q);
-            else w = *(const unsigned char*)(row + q);
-            sum_word<DT>(w, acc, iacc, bad);  // zero upper parts contribute 0
-        }
-    }
-}
-
-__device__ __forceinline__ void wave_reduce(double& acc, uint64_t& iacc, int& bad) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        acc += __shfl_xor(acc, off);
-        iacc += __shfl_xor(iacc, off);
-        bad += __shfl_xor(bad, off);
-    }
-}
 
 template <int DT>
 __global__ __launch_bounds__(256) void ps_sums_kernel(const void* V, int64_t n_f, int64_t n_v,
@@ -93,14 +17,10 @@ __global__ __launch_bounds__(256) void ps_sums_kernel(const void* V, int64_t n_f
     // one wave per vector, waves striding over the vectors (no block barrier)
     for (int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64; i < n_v;
          i += (int64_t)gridDim.x * 4) {
-        const char* row = (const char*)V + i * ld * ESZ;
-        double acc = 0.0;
-        uint64_t iacc = 0;
         int nbad = 0;
-        sum_row<DT>(row, n_f, vec, acc, iacc, nbad);
-        wave_reduce(acc, iacc, nbad);
+        const double x = wave_row_sum<DT>((const char*)V + i * ld * ESZ, n_f, vec, nbad);
         if (threadIdx.x % 64 == 0) {
-            s[i] = DT == PS_U8 ? (double)iacc : acc;
+            s[i] = x;
             if (bad && nbad) atomicAdd(bad, nbad);
         }
     }
@@ -116,13 +36,10 @@ __global__ __launch_bounds__(256) void ps_batched_sums_kernel(const DevProblem* 
     const bool vec = ((uintptr_t)pr.V % 16 == 0) && ((pr.ld * ESZ) % 16 == 0);
     for (int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64; i < pr.n_v;
          i += (int64_t)gridDim.x * 4) {
-        const char* row = (const char*)pr.V + i * pr.ld * ESZ;
-        double acc = 0.0;
-        uint64_t iacc = 0;
         int nbad = 0;
-        sum_row<DT>(row, pr.n_f, vec, acc, iacc, nbad);
-        wave_reduce(acc, iacc, nbad);
-        if (threadIdx.x % 64 == 0) ((double*)pr.s)[i] = DT == PS_U8 ? (double)iacc : acc;
+        const double x =
+            wave_row_sum<DT>((const char*)pr.V + i * pr.ld * ESZ, pr.n_f, vec, nbad);
+        if (threadIdx.x % 64 == 0) ((double*)pr.s)[i] = x;
     }
 }
 
@@ -433,6 +350,7 @@ hipError_t launch_prefix3(int64_t n_v, int64_t jb, int64_t je, int bm, int mode,
 }
 
 hipError_t launch_mg3_prefix(const Mg3Launch& a, hipStream_t st) {
+    if (a.small) return hipSuccess;
     const int bm = kValuCfgs[a.cfg].bm();
     if (a.mode == kSlabFlat) return launch_prefix3_flat(a.n_v, a.j_begin, a.j_end, bm, a.prefix, st);
     if (a.mode == kSlabSplit)

@@ -18,6 +18,8 @@
 // the tetrahedron, past n_v) skips the arithmetic but still helps stage.
 #pragma once
 
+#include <type_traits>
+
 #include "ps_internal.h"
 
 #ifndef PS_UNROLL_PLAIN
@@ -484,8 +486,46 @@ __device__ __forceinline__ void tri_decode(int64_t t, int64_t& bi, int64_t& bj) 
 // Epilogues.
 // ---------------------------------------------------------------------------
 
-// 2-way: c2 = 2 n2 / (s_i + s_j) in FP64 (Section 2.1), rounded once to FP32;
-// optional raw numerators.  Output (i, j), i < j, at colex j(j-1)/2 + i.
+// n3' of a uint8 slice sum (see the slices in mgemm_kernels.h).
+__device__ __forceinline__ uint32_t u8_min_sum(uint32_t sad, int32_t n2_pair, double s_single) {
+    return (uint32_t)(((int64_t)n2_pair + (int64_t)s_single - (int64_t)sad) / 2);
+}
+
+// Type of the pair numerators n2.
+template <int DT>
+using PairT = typename std::conditional<
+    DT == PS_U8 || DT == PS_B1, int32_t,
+    typename std::conditional<DT == PS_F64, double, float>::type>::type;
+
+
+// One pair's outputs at packed index idx from its kernel sum: c2 = 2 n2 / (s_i
+// + s_j) in FP64 (Section 2.1), rounded once to FP32; optional raw numerators.
+template <int DT>
+__device__ __forceinline__ void store_pair(typename Ops<DT>::Acc acc, double si, double sj,
+                                           int64_t idx, float* c2, void* n2) {
+    double num;
+    if constexpr (DT == PS_U8) {
+        const int64_t v = ((int64_t)si + (int64_t)sj - (int64_t)acc) / 2;
+        num = (double)v;
+        if (n2) ((int32_t*)n2)[idx] = (int32_t)v;
+    } else if constexpr (DT == PS_B1) {
+        num = (double)acc;
+        if (n2) ((int32_t*)n2)[idx] = (int32_t)acc;
+    } else if constexpr (DT == PS_F64) {
+        num = acc;
+        if (n2) ((double*)n2)[idx] = acc;
+    } else {
+        num = (double)acc;
+        if (n2) ((float*)n2)[idx] = acc;
+    }
+    if (c2) {
+        const double d = si + sj;
+        c2[idx] = d > 0.0 ? (float)((2.0 * num) / d) : 0.0f;
+    }
+}
+
+// 2-way: the outputs of a lane's micro-tile.  Output (i, j), i < j, at colex
+// j(j-1)/2 + i.
 template <int DT, int TM, int TN>
 __device__ __forceinline__ void epilogue2(const typename Ops<DT>::Acc (&acc)[TM][TN],
                                           int64_t row0, int64_t col0, int64_t n_v,
@@ -508,26 +548,7 @@ __device__ __forceinline__ void epilogue2(const typename Ops<DT>::Acc (&acc)[TM]
         for (int c = 0; c < TN; ++c) {
             const int64_t j = col0 + lane_col<TN>(wave, ly, c);
             if (j >= n_v || i >= j) continue;
-            const int64_t idx = j * (j - 1) / 2 + i;
-            double num;
-            if constexpr (DT == PS_U8) {
-                const int64_t v = ((int64_t)si + (int64_t)sc[c] - (int64_t)acc[r][c]) / 2;
-                num = (double)v;
-                if (n2) ((int32_t*)n2)[idx] = (int32_t)v;
-            } else if constexpr (DT == PS_B1) {
-                num = (double)acc[r][c];
-                if (n2) ((int32_t*)n2)[idx] = (int32_t)acc[r][c];
-            } else if constexpr (DT == PS_F64) {
-                num = acc[r][c];
-                if (n2) ((double*)n2)[idx] = acc[r][c];
-            } else {
-                num = (double)acc[r][c];
-                if (n2) ((float*)n2)[idx] = acc[r][c];
-            }
-            if (c2) {
-                const double d = si + sc[c];
-                c2[idx] = d > 0.0 ? (float)((2.0 * num) / d) : 0.0f;
-            }
+            store_pair<DT>(acc[r][c], si, sc[c], j * (j - 1) / 2 + i, c2, n2);
         }
     }
 }

@@ -3,7 +3,7 @@
 // mg_u8.hip) includes this once and instantiates the launchers for its type.
 #pragma once
 
-#include "mgemm_core.h"
+#include "mgemm_small.h"
 
 namespace ps {
 
@@ -95,10 +95,6 @@ __global__ __launch_bounds__(kThreads, PS_MIN_WAVES) void ps_mg2_kernel(Mg2Launc
 // n3' = sum_q min(x_q, y_q) = (n2(a, b) + s_y - SAD) / 2 instead, from the
 // pair's numerator and the single vector's sum, so the finish need not know
 // which pair was staged.
-__device__ __forceinline__ uint32_t u8_min_sum(uint32_t sad, int32_t n2_pair, double s_single) {
-    return (uint32_t)(((int64_t)n2_pair + (int64_t)s_single - (int64_t)sad) / 2);
-}
-
 // 3-way over pair rows (kSlabFlat, and part 0 of kSlabSplit): one workgroup
 // per (row tile of BM consecutive pairs (i, j) in colex order, column tile of
 // BM k's from the row tile's first j + 1, field chunk).  The A operand row of
@@ -268,9 +264,7 @@ constexpr int kFinishRange = 2048;
 template <int DT>
 __global__ __launch_bounds__(256) void ps_c3_finish_kernel(Mg3Launch a, int64_t nitems,
                                                            int64_t item0) {
-    using N2T = typename std::conditional<
-        DT == PS_U8 || DT == PS_B1, int32_t,
-        typename std::conditional<DT == PS_F64, double, float>::type>::type;
+    using N2T = PairT<DT>;
     const int64_t b = item0 + blockIdx.x;
     if (b >= nitems) return;
     int64_t lo = 0, hi = a.j_end - a.j_begin;   // slab holding range b (see ps_mg3_kernel)
@@ -334,6 +328,7 @@ __global__ __launch_bounds__(256) void ps_c3_finish_kernel(Mg3Launch a, int64_t 
 template <int DT>
 hipError_t go_c3_finish(const Mg3Launch& a, hipStream_t st) {
     if (a.j_end <= a.j_begin) return hipSuccess;
+    if (a.small && (a.nchunks == 1 || DT == PS_F64)) return hipSuccess;   // Eq. 1 in the slices
     hipError_t e = launch_prefix3(a.n_v, a.j_begin, a.j_end, kFinishRange, kSlabRange, 0,
                                   a.prefix, st);
     if (e != hipSuccess) return e;
@@ -395,6 +390,7 @@ __global__ __launch_bounds__(kThreads, PS_MIN_WAVES) void ps_mgb_kernel(MgBatchL
 
 template <int DT, int TM, int BKW>
 hipError_t go_mg2(const Mg2Launch& a, hipStream_t st) {
+    if (a.small) return go_sm2<DT>(a, st);
     const int64_t T = shard_tiles(tri_tiles(a.n_v, 16 * TM), a.shard0, a.nshards);
     if (T == 0) return hipSuccess;
     return launch_items(T * a.nchunks, kThreads, kXcds, [&](unsigned grid, int64_t item0) {
@@ -417,6 +413,7 @@ hipError_t go_mg3(const Mg3Launch& a, hipStream_t st) {
 // configuration cfg.
 template <int DT, class Dispatch>
 hipError_t go_mg3_all(const Mg3Launch& a, Dispatch dispatch, hipStream_t st) {
+    if (a.small) return go_sm3<DT>(a, st);
     return dispatch(a.cfg, [&](auto tm, auto bkw) {
         return go_mg3<DT, decltype(tm)::value, decltype(bkw)::value>(a, st);
     });

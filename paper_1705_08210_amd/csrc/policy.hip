@@ -51,6 +51,36 @@ int choose_cfg(int32_t dt, int32_t way, int32_t path, int64_t n_f, int64_t n_v,
     return default_cfg(way, n_v);
 }
 
+// The 32 x 32 field-split tiles pay while the 64 x 64 tiles (x field chunks)
+// leave the chip short of workgroups; past that their double operand traffic
+// per output shows.  Whole calls, us, 64 x 64 / 32 x 32:
+//   FP32 (split over field chunks): 1001 fields, 1024 vectors 51 / 40 (1088
+//     items), 1500 85 / 75, 2048 121 / 114; 12000 fields, 256 vectors 75 / 65
+//     (940 items), 512 122 / 127 (2052 items)
+//   FP64 (never split): 4096 fields, 700 vectors 529 / 119, 2048 983 / 730 (528
+//     tiles), 3000 1518 / 1407
+//   uint8: 4096 fields, 700 vectors 81 / 24, 2048 138 / 105; 1001 fields, 1500
+//     40 / 35, 2048 50 / 52
+// Eight waves while all workgroups find a CU of their own (FP64, 4096 fields:
+// 700 vectors 119 against 162 with four, 1024 324 against 276).
+int small2(int32_t dt, int64_t n_f, int64_t n_v, int cfg, int32_t nchunks, const ps_opts* o) {
+    if ((o && o->tile > 0) || cfg != 1) return 0;
+    const int64_t limit = dt == PS_F32 || dt == PS_F16 ? 1200
+                          : dt == PS_U8 && n_f < 2048  ? 300
+                                                       : 560;
+    if (tri_tiles(n_v, 64) * nchunks > limit) return 0;
+    return tri_tiles(n_v, 32) * nchunks <= 320 ? 8 : 4;
+}
+
+// As small2 for the slices (the rule looks at the vectors alone, so that a
+// stage sums as the whole run does).  FP32, us, 64 x 64 tiles and finish / 32 x
+// 32: 385 fields, 64 vectors 79 / 25, 150 85 / 44, 200 95 / 61, 255 134 / 121;
+// 8000 fields, 64 vectors 474 / 132, 200 850 / 820, 255 1389 / 2089.
+int small3(int64_t n_v, const ps_opts* o) {
+    if ((o && o->tile > 0) || n_v > 208) return 0;
+    return n_v <= 96 ? 8 : 4;
+}
+
 int choose_acc(int64_t n_f, const ps_opts* o) {
     const int a = o ? o->acc : PS_ACC_AUTO;
     if (a == PS_ACC_PLAIN || a == PS_ACC_BLOCKED) return a;

@@ -286,8 +286,12 @@ static ps_status ps2_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
         if (e == hipSuccess) e = launch_bp2(b, stream);
         return e == hipSuccess ? PS_OK : hip_fail(e, "2-way bit planes launch");
     }
+    const int small = is_mfma(path) || bits ? 0 : small2(dtype, n_f, n_v, cfg, sp.nchunks, opts);
+    // field-split small tiles need the sums only in the finish: one launch does both
+    const bool with_sums = !s && small && sp.nchunks > 1;
     if (!s) {
-        e = launch_sums(V, dtype, n_f, n_v, ld, s_ws, nullptr, stream);
+        if (!with_sums) e = launch_sums(V, dtype, n_f, n_v, ld, s_ws, nullptr, stream);
+        else e = hipSuccess;
         if (e != hipSuccess) return hip_fail(e, "sums launch");
         s = s_ws;
     }
@@ -308,8 +312,9 @@ static ps_status ps2_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
         e = launch_mg2(PS_B1, a, stream);
         return e == hipSuccess ? PS_OK : hip_fail(e, "2-way bits launch");
     }
-    Mg2Launch a{V,         n_f,           n_v,     ld,    s,      c2, n2, cfg,
-                sp.nchunks, sp.chunk_tiles, partial, shard, nshards};
+    Mg2Launch a{V,         n_f,           n_v,     ld,    s,       c2,    n2,
+                cfg,       sp.nchunks,    sp.chunk_tiles, partial, shard, nshards,
+                small,     with_sums ? s_ws : nullptr};
     e = launch_mg2(dtype, a, stream);
     if (e == hipSuccess && sp.nchunks > 1) e = launch_finish2(dtype, a, stream);
     return e == hipSuccess ? PS_OK : hip_fail(e, "2-way launch");
@@ -611,9 +616,12 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
     if (ws_bytes < need || !workspace)
         return fail(PS_ERR_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, need);
     if (!aligned(workspace, 256)) return fail(PS_ERR_ARG, "workspace is not 256-byte aligned");
-    hipError_t e;
+    hipError_t e = hipSuccess;
+    const int pair_small = bits ? 0 : small2(dtype, n_f, n_v, cfg2, sp2.nchunks, opts);
+    // floating pair numerators need no sums: their small tiles carry the sums along
+    const bool with_sums = !s && !n2 && pair_small && dtype != PS_U8;
     if (!s) {
-        e = launch_sums(V, dtype, n_f, n_v, ld, s_ws, nullptr, stream);
+        if (!with_sums) e = launch_sums(V, dtype, n_f, n_v, ld, s_ws, nullptr, stream);
         if (e != hipSuccess) return hip_fail(e, "sums launch");
         s = s_ws;
     }
@@ -627,8 +635,8 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
         kn_f = kld = bits_row_words(n_f);
     }
     if (!n2) {  // the pair numerators of Eq. 1 (the 2-way mGEMM prepass)
-        Mg2Launch a{KV, kn_f, n_v, kld, s, nullptr, n2_ws, cfg2, sp2.nchunks, sp2.chunk_tiles,
-                    partial};
+        Mg2Launch a{KV,      kn_f, n_v, kld, s, nullptr, n2_ws, cfg2, sp2.nchunks, sp2.chunk_tiles,
+                    partial, 0,    1,   pair_small, with_sums ? s_ws : nullptr};
         e = launch_mg2(kdt, a, stream);
         if (e == hipSuccess && sp2.nchunks > 1) e = launch_finish2(dtype, a, stream);
         if (e != hipSuccess) return hip_fail(e, "3-way numerator prepass launch");
@@ -639,11 +647,12 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
     // one launch over the split tiling of the stage: colex (pair, k) tiles of
     // the slabs below js, lex (pair, i) tiles of the others
     const int64_t js = split3(n_v, j_begin, j_end);
-    const int64_t nt0 = flat_tiles(n_v, j_begin, js, bm);
+    const int small = small3(n_v, opts);
+    const int64_t nt0 = small ? 0 : flat_tiles(n_v, j_begin, js, bm);
     Mg3Launch a{KV, kn_f, n_v, kld, s, n2, j_begin, j_end, c3, prefix,
-                nt0 + lex_tiles(n_v, js, j_end, bm), cfg, nchunks,
-                bits ? 0 : chunk_tiles(dtype, cfg), partial, kSlabSplit,
-                js, nt0, prefix + flat_row_tiles(j_begin, js, bm) + 1};
+                small ? 0 : nt0 + lex_tiles(n_v, js, j_end, bm), cfg, nchunks,
+                bits ? 0 : chunk_tiles(dtype, small ? 1 : cfg), partial, kSlabSplit,
+                js, nt0, prefix + flat_row_tiles(j_begin, js, bm) + 1, small};
     e = launch_mg3_prefix(a, stream);
     if (e == hipSuccess) e = launch_mg3(kdt, a, stream);
     return e == hipSuccess ? PS_OK : hip_fail(e, "3-way launch");

@@ -267,6 +267,11 @@ constexpr int64_t kMinItems = 2048;      // ~8 workgroups per CU
 constexpr int64_t kMinChunkTiles = 4;
 int choose_cfg(int32_t dt, int32_t way, int32_t path, int64_t n_f, int64_t n_v,
                const ps_opts* o);
+// Waves per workgroup (4 or 8) if a 2-way launch with configuration cfg, or a
+// 3-way launch, runs the 32 x 32 tiles of mgemm_small.h (o->tile = 0 only);
+// 0 if not.
+int small2(int32_t dt, int64_t n_f, int64_t n_v, int cfg, int32_t nchunks, const ps_opts* o);
+int small3(int64_t n_v, const ps_opts* o);
 int choose_acc(int64_t n_f, const ps_opts* o);
 int32_t split_chunks(int32_t dt, int64_t n_f, int acc);
 int64_t chunk_tiles(int32_t dt, int cfg);
@@ -307,6 +312,10 @@ struct Mg2Launch {
     // tile shard: only the tiles t = shard0 + u * nshards of the upper
     // triangle (nshards <= 1: all tiles)
     int64_t shard0, nshards;
+    // small: waves of the 32 x 32 tiles of mgemm_small.h instead of cfg's 64 x 64
+    // (same chunks), or 0; s_out: the launch also writes the per-vector sums there
+    int32_t small;
+    double* s_out;
 };
 
 // Tiles of the upper triangle in shard shard0 of nshards (tri_tiles when
@@ -337,6 +346,7 @@ struct Mg3Launch {
     // slabs [js, j_end) lex-ordered (the other tiles, prefix1)
     int64_t js, ntiles0;
     int64_t* prefix1;
+    int32_t small;               // waves of the 32 x 32 tiles of mgemm_small.h (no prefix), or 0
 };
 
 // Device problem record of a batched launch.
