@@ -350,7 +350,7 @@ hipError_t launch_prefix3(int64_t n_v, int64_t jb, int64_t je, int bm, int mode,
 }
 
 hipError_t launch_mg3_prefix(const Mg3Launch& a, hipStream_t st) {
-    if (a.small) return hipSuccess;
+    if (slab_small(a.mode)) return hipSuccess;
     const int bm = kValuCfgs[a.cfg].bm();
     if (a.mode == kSlabFlat) return launch_prefix3_flat(a.n_v, a.j_begin, a.j_end, bm, a.prefix, st);
     if (a.mode == kSlabSplit)

@@ -328,7 +328,8 @@ __global__ __launch_bounds__(256) void ps_c3_finish_kernel(Mg3Launch a, int64_t 
 template <int DT>
 hipError_t go_c3_finish(const Mg3Launch& a, hipStream_t st) {
     if (a.j_end <= a.j_begin) return hipSuccess;
-    if (a.small && (a.nchunks == 1 || DT == PS_F64)) return hipSuccess;   // Eq. 1 in the slices
+    if (slab_small(a.mode) && (a.nchunks == 1 || DT == PS_F64))
+        return hipSuccess;   // Eq. 1 ran in the slices
     hipError_t e = launch_prefix3(a.n_v, a.j_begin, a.j_end, kFinishRange, kSlabRange, 0,
                                   a.prefix, st);
     if (e != hipSuccess) return e;
@@ -413,7 +414,7 @@ hipError_t go_mg3(const Mg3Launch& a, hipStream_t st) {
 // configuration cfg.
 template <int DT, class Dispatch>
 hipError_t go_mg3_all(const Mg3Launch& a, Dispatch dispatch, hipStream_t st) {
-    if (a.small) return go_sm3<DT>(a, st);
+    if (slab_small(a.mode)) return go_sm3<DT>(a, st);
     return dispatch(a.cfg, [&](auto tm, auto bkw) {
         return go_mg3<DT, decltype(tm)::value, decltype(bkw)::value>(a, st);
     });

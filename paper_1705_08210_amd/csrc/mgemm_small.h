@@ -345,7 +345,7 @@ bool sm_vec(const void* V, int64_t ld) {
     return (uintptr_t)V % 16 == 0 && ld * Ops<DT>::kEsz % 16 == 0;
 }
 
-// a.small: the waves of a workgroup, 4 or 8.
+// waves: of a workgroup, 4 or 8.
 template <int DT, class Go>
 hipError_t sm_dispatch(const void* V, int64_t ld, int waves, Go go) {
     const bool vec = (uintptr_t)V % 16 == 0 && ld * Ops<DT>::kEsz % 16 == 0;
@@ -377,7 +377,7 @@ hipError_t go_sm3(const Mg3Launch& a, hipStream_t st) {
     g.cols0 = ceil_div(a.n_v - 1 - a.j_begin, kSmB);   // the first row tile's
     g.rows1 = lex_row_tiles(a.n_v, a.js, a.j_end, kSmB);
     g.cols1 = ceil_div(a.j_end - 1, kSmB);             // the last row tile's
-    return sm_dispatch<DT>(a.V, a.ld, a.small, [&](auto nw, auto vec) {
+    return sm_dispatch<DT>(a.V, a.ld, a.mode == kSlabSmall8 ? 8 : 4, [&](auto nw, auto vec) {
         constexpr int NW = decltype(nw)::value;
         return launch_items(g.items() * a.nchunks, 64 * NW, 1, [&](unsigned grid, int64_t item0) {
             hipLaunchKernelGGL((ps_sm3_kernel<DT, NW, decltype(vec)::value>), dim3(grid),

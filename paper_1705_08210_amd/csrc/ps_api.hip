@@ -651,8 +651,9 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
     const int64_t nt0 = small ? 0 : flat_tiles(n_v, j_begin, js, bm);
     Mg3Launch a{KV, kn_f, n_v, kld, s, n2, j_begin, j_end, c3, prefix,
                 small ? 0 : nt0 + lex_tiles(n_v, js, j_end, bm), cfg, nchunks,
-                bits ? 0 : chunk_tiles(dtype, small ? 1 : cfg), partial, kSlabSplit,
-                js, nt0, prefix + flat_row_tiles(j_begin, js, bm) + 1, small};
+                bits ? 0 : chunk_tiles(dtype, small ? 1 : cfg), partial,
+                small == 8 ? kSlabSmall8 : small ? kSlabSmall4 : kSlabSplit,
+                js, nt0, prefix + flat_row_tiles(j_begin, js, bm) + 1};
     e = launch_mg3_prefix(a, stream);
     if (e == hipSuccess) e = launch_mg3(kdt, a, stream);
     return e == hipSuccess ? PS_OK : hip_fail(e, "3-way launch");

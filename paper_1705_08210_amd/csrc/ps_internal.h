@@ -79,8 +79,13 @@ __host__ __device__ inline int64_t slab_offset(int64_t n, int64_t j) {
 // stage (flat_* below).  kSlabSplit (the VALU slices): kSlabFlat over the
 // slabs below the split point split3, then the lex-ordered tiling (lex_*
 // below) over the rest, in one launch.  The per-slab sets serve the
-// matrix-core slices' per-slab tiling and the finish.
-enum { kSlabAll = 0, kSlabFull = 1, kSlabEdge = 2, kSlabRange = 3, kSlabFlat = 4, kSlabSplit = 5 };
+// matrix-core slices' per-slab tiling and the finish.  kSlabSmall4 / 8: the
+// split tiling in the 32 x 32 tiles of mgemm_small.h, four or eight waves (a
+// mode and not a field of Mg3Launch: with one more field the compiler gave the
+// FP32 64 x 64 slices 127 registers instead of 78, 28.4 -> 30.8 ms on
+// sparse_4096x1024).
+enum { kSlabAll = 0, kSlabFull = 1, kSlabEdge = 2, kSlabRange = 3, kSlabFlat = 4, kSlabSplit = 5,
+       kSlabSmall4 = 6, kSlabSmall8 = 7 };
 
 // Pair (i, j), i < j, has colex index p = j (j - 1) / 2 + i.  pair_j(p) is
 // its j: the largest j with j (j - 1) / 2 <= p.
@@ -325,6 +330,8 @@ inline int64_t shard_tiles(int64_t T, int64_t shard0, int64_t nshards) {
     return T > shard0 ? (T - shard0 + nshards - 1) / nshards : 0;
 }
 
+inline bool slab_small(int mode) { return mode == kSlabSmall4 || mode == kSlabSmall8; }
+
 // Arguments of one 3-way launch over the tiles of middle indices
 // [j_begin, j_end).
 struct Mg3Launch {
@@ -341,12 +348,12 @@ struct Mg3Launch {
     int64_t chunk_tiles;         // holds nchunks * stage-size FP32 values (for
     float* partial;              // PS_F64: stage-size doubles of raw n3', no split)
     int32_t mode;                // tile set of the slice launch: kSlabFlat (prefix over the
-                                 // colex row tiles) or kSlabSplit; kSlabAll for the finish
+                                 // colex row tiles), kSlabSplit or kSlabSmall4 / 8 (no
+                                 // prefix); kSlabAll for the finish
     // kSlabSplit: slabs [j_begin, js) as kSlabFlat (tiles [0, ntiles0), prefix),
     // slabs [js, j_end) lex-ordered (the other tiles, prefix1)
     int64_t js, ntiles0;
     int64_t* prefix1;
-    int32_t small;               // waves of the 32 x 32 tiles of mgemm_small.h (no prefix), or 0
 };
 
 // Device problem record of a batched launch.
