@@ -164,7 +164,7 @@ def cpu_baseline(V, n_f, seconds, way, seed=123):
 # digest stamps a recorded HBM-traffic figure, which is reported only while
 # the sources are unchanged.
 CSRC = os.path.join(ROOT, "paper_1705_08210_amd", "csrc")
-_VALU_SOURCES = ["ps_internal.h", "mgemm_core.h", "mgemm_kernels.h", "mgemm_small.h", "sums.h", "mg_common.hip",
+_VALU_SOURCES = ["ps_internal.h", "mgemm_core.h", "mgemm_kernels.h", "mgemm_small.h", "mgemm_half.h", "sums.h", "mg_common.hip",
                  "mg_f32.hip", "mg_f16.hip", "mg_u8.hip", "policy.hip"]
 _MFMA_SOURCES = ["ps_internal.h", "mfma_tile.h", "mfma.hip", "policy.hip"]
 _BITS_SOURCES = ["ps_internal.h", "mfma_tile.h", "bitplane.hip", "policy.hip"]

@@ -27,7 +27,7 @@ LIB = os.path.join(PKG, "libps.so")
 
 SOURCES = ["ps_api.hip", "policy.hip", "mg_common.hip", "mg_f32.hip", "mg_f16.hip", "mg_u8.hip",
            "mg_b1.hip", "mg_f64.hip", "mfma.hip", "bitplane.hip", "reduce.hip", "probe.hip"]
-HEADERS = ["ps_internal.h", "mfma_tile.h", "mgemm_core.h", "mgemm_kernels.h", "mgemm_small.h",
+HEADERS = ["ps_internal.h", "mfma_tile.h", "mgemm_core.h", "mgemm_kernels.h", "mgemm_small.h", "mgemm_half.h",
            "sums.h"]
 
 ARCH = os.environ.get("PS_OFFLOAD_ARCH", "gfx950")

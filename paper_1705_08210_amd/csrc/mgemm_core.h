@@ -3,7 +3,8 @@
 //   acc[r][c] = sum_q op(A[row r, q], B[col c, q])
 // where both operands are vectors of V (field-contiguous rows) and
 //   PS_F32: op = min,                      FP32 accumulation
-//   PS_F16: op = packed FP16 min, summed by a dot product with (1, 1) into FP32
+//   PS_F16: op = packed FP16 min, FP32 accumulation on the matrix cores
+//           (mgemm_half.h; the small tiles: by dot products with (1, 1))
 //   PS_U8 : op = |a - b| summed four bytes at a time (v_sad_u8); the pair
 //           numerator follows from min(a,b) = (a + b - |a-b|) / 2.
 //   PS_B1 : binary fields, 32 per word; op = popcount(a AND b).
@@ -20,6 +21,7 @@
 
 #include <type_traits>
 
+#include "mgemm_half.h"
 #include "ps_internal.h"
 
 #ifndef PS_UNROLL_PLAIN
@@ -141,6 +143,8 @@ struct Stager {
     static constexpr int kCh = BM * kCpr / kThreads;     // chunks per thread
     static constexpr int kLd = BM + 4;                   // LDS row pitch (words)
     static_assert(BM * kCpr % kThreads == 0, "tile not divisible");
+    static constexpr int kLdsWords = BKW * kLd;          // words of a staged tile
+    __device__ static int row(int c) { return (threadIdx.x + c * kThreads) % BM; }
     uint4 r[kCh];
 
     // Load the 16-byte chunk that straddles the end of the fields, element by
@@ -255,6 +259,12 @@ struct Stager {
     }
 };
 
+// The staging geometry of a storage type's tiles: kCh chunks per thread, row(c)
+// the tile row of chunk c, kLdsWords LDS words per operand.
+template <int DT, int TM, int BKW>
+using TileGeom = typename std::conditional<
+    DT == PS_F16, HalfGeom<TM, BKW>, Stager<16 * TM, BKW, typename Ops<DT>::Word>>::type;
+
 // Rows/columns of a lane's micro-tile element (r, c) relative to the tile.
 template <int TM>
 __device__ __forceinline__ int lane_row(int wave, int lx, int r) {
@@ -264,6 +274,40 @@ template <int TN>
 __device__ __forceinline__ int lane_col(int wave, int ly, int c) {
     return (wave >> 1) * (8 * TN) + (c / 4) * 32 + ly * 4 + (c % 4);
 }
+
+// Waves per SIMD a tile kernel is compiled for.  The FP16 128 x 128 tiles with
+// 16-word field tiles fit three (168 registers) with their chunk loop rolled:
+// 15.70 -> 15.41 ms (20000 x 8191 2-way), 18.60 -> 18.25 ms (4096 x 1024 3-way).
+template <int DT, int TM, int BKW>
+constexpr int min_waves() { return DT == PS_F16 && TM == 8 && BKW == 16 ? 3 : PS_MIN_WAVES; }
+
+// The outputs a lane holds: kR x kC elements, (r, c) at tile row row(r), column
+// col(c).
+template <int DT, int TM>
+struct Micro {
+    static constexpr int kR = TM, kC = TM;
+    __device__ __forceinline__ static int row(int wave, int lane, int r) {
+        return lane_row<TM>(wave, lane % 8, r);
+    }
+    __device__ __forceinline__ static int col(int wave, int lane, int c) {
+        return lane_col<TM>(wave, lane / 8, c);
+    }
+};
+// FP16 (mgemm_half.h): register e of lane l in D[r][q] is output 4 q + l % 16 / 4
+// of lane l' = 4 (l / 16) + e + 16 (l % 4), in row 8 r + l' % 8 and column 8
+// (4 q + l % 16 / 4) + l' / 8 of the wave's quadrant.
+template <int TM>
+struct Micro<PS_F16, TM> {
+    static constexpr int kR = 4 * TM, kC = TM / 4;
+    __device__ __forceinline__ static int row(int wave, int l, int r) {
+        return (wave & 1) * (8 * TM) + r / 4 * 8 + (l / 16 & 1) * 4 + r % 4;
+    }
+    __device__ __forceinline__ static int col(int wave, int l, int c) {
+        return (wave >> 1) * (8 * TM) + 32 * c + l % 16 / 4 * 8 + l / 32 + l % 4 * 2;
+    }
+};
+template <int DT, int TM>
+using MicroAcc = typename Ops<DT>::Acc[Micro<DT, TM>::kR][Micro<DT, TM>::kC];
 
 // ---------------------------------------------------------------------------
 // One output tile.  acc receives the sums for the lane's micro-tile.
@@ -351,22 +395,66 @@ __device__ __forceinline__ void run_tile_body(const char* Vb, int64_t ldb, int64
     }
 }
 
+// The FP16 tile: rows ra / xa / rb as in half_tile, field tiles [kt0, kt1) (kt1 <
+// 0: all of them).
+template <int TM, int BKW, bool XJ, bool VEC>
+__device__ __forceinline__ void run_half(const char* Vb, int64_t nbytes,
+                                         const int64_t (&ra)[HalfGeom<TM, BKW>::kCh],
+                                         const int64_t (&xa)[HalfGeom<TM, BKW>::kCh],
+                                         const int64_t (&rb)[HalfGeom<TM, BKW>::kCh], bool active,
+                                         uint32_t* As, uint32_t* Bs, MicroAcc<PS_F16, TM>& acc,
+                                         int64_t kt0, int64_t kt1) {
+    using S = Stager<16 * TM, BKW>;
+    const int64_t nk_all = (nbytes + BKW * 4 - 1) / (BKW * 4);
+    f4_t D[TM][TM / 4];
+    half_tile<TM, BKW, XJ, VEC>(Vb, nbytes, ra, xa, rb, active, (uint4*)As, (uint4*)Bs, D, kt0,
+                           kt1 < 0 || kt1 > nk_all ? nk_all : kt1,
+                           [](const char* p, int64_t left) {
+                               return S::template load_chunk<2, VEC>(p, 0, left);
+                           });
+#pragma unroll
+    for (int r = 0; r < 4 * TM; ++r)
+#pragma unroll
+        for (int c = 0; c < TM / 4; ++c) acc[r][c] = D[r / 4][c][r % 4];
+}
+
+// Byte offsets of the staged rows [row0, end) of a FP16 tile.
+template <int TM, int BKW>
+__device__ __forceinline__ void half_rows(int64_t row0, int64_t end, int64_t ldb,
+                                          int64_t (&ro)[HalfGeom<TM, BKW>::kCh]) {
+#pragma unroll
+    for (int c = 0; c < HalfGeom<TM, BKW>::kCh; ++c) {
+        const int64_t g = row0 + HalfGeom<TM, BKW>::row(c);
+        ro[c] = (g < end ? g : end - 1) * ldb;
+    }
+}
+
 // One output tile; the row alignment picks the staging loads once for the
 // whole field loop (see Stager::load_chunk).
-template <int DT, int TM, int TN, int BKW, bool XJ>
+template <int DT, int TM, int BKW>
 __device__ __forceinline__ void run_tile(const char* Vb, int64_t ldb, int64_t nbytes,
                                          bool vec, int64_t a_row0, int64_t a_end,
-                                         int64_t b_row0, int64_t b_end, const char* xrow,
+                                         int64_t b_row0, int64_t b_end,
                                          bool active, typename Ops<DT>::Word* As,
                                          typename Ops<DT>::Word* Bs,
-                                         typename Ops<DT>::Acc (&acc)[TM][TN],
+                                         MicroAcc<DT, TM>& acc,
                                          int64_t kt0 = 0, int64_t kt1 = -1) {
-    if (vec)
-        run_tile_body<DT, TM, TN, BKW, XJ, true>(Vb, ldb, nbytes, a_row0, a_end, b_row0, b_end,
-                                                 xrow, active, As, Bs, acc, kt0, kt1);
-    else
-        run_tile_body<DT, TM, TN, BKW, XJ, false>(Vb, ldb, nbytes, a_row0, a_end, b_row0,
-                                                  b_end, xrow, active, As, Bs, acc, kt0, kt1);
+    if constexpr (DT == PS_F16) {
+        int64_t ra[HalfGeom<TM, BKW>::kCh], rb[HalfGeom<TM, BKW>::kCh];
+        half_rows<TM, BKW>(a_row0, a_end, ldb, ra);
+        half_rows<TM, BKW>(b_row0, b_end, ldb, rb);
+        if (vec)
+            run_half<TM, BKW, false, true>(Vb, nbytes, ra, ra, rb, active, As, Bs, acc, kt0, kt1);
+        else
+            run_half<TM, BKW, false, false>(Vb, nbytes, ra, ra, rb, active, As, Bs, acc, kt0, kt1);
+    } else if (vec) {
+        run_tile_body<DT, TM, TM, BKW, false, true>(Vb, ldb, nbytes, a_row0, a_end, b_row0, b_end,
+                                                    nullptr, active, As, Bs, acc, kt0, kt1);
+    } else {
+        run_tile_body<DT, TM, TM, BKW, false, false>(Vb, ldb, nbytes, a_row0, a_end, b_row0,
+                                                     b_end, nullptr, active, As, Bs, acc, kt0,
+                                                     kt1);
+    }
 }
 
 // run_tile for the flattened 3-way slices: the A rows are given per staged
@@ -450,19 +538,29 @@ __device__ __forceinline__ void run_tile_flat_body(
     }
 }
 
-template <int DT, int TM, int TN, int BKW>
+template <int DT, int TM, int BKW>
 __device__ __forceinline__ void run_tile_flat(
     const char* Vb, int64_t ldb, int64_t nbytes, bool vec,
-    const int64_t (&aoff)[Stager<16 * TM, BKW, typename Ops<DT>::Word>::kCh],
-    const int64_t (&xoff)[Stager<16 * TM, BKW, typename Ops<DT>::Word>::kCh], int64_t b_row0,
+    const int64_t (&aoff)[TileGeom<DT, TM, BKW>::kCh],
+    const int64_t (&xoff)[TileGeom<DT, TM, BKW>::kCh], int64_t b_row0,
     int64_t b_end, bool active, typename Ops<DT>::Word* As, typename Ops<DT>::Word* Bs,
-    typename Ops<DT>::Acc (&acc)[TM][TN], int64_t kt0 = 0, int64_t kt1 = -1) {
-    if (vec)
-        run_tile_flat_body<DT, TM, TN, BKW, true>(Vb, ldb, nbytes, aoff, xoff, b_row0, b_end,
+    MicroAcc<DT, TM>& acc, int64_t kt0 = 0, int64_t kt1 = -1) {
+    if constexpr (DT == PS_F16) {
+        int64_t rb[HalfGeom<TM, BKW>::kCh];
+        half_rows<TM, BKW>(b_row0, b_end, ldb, rb);
+        if (vec)
+            run_half<TM, BKW, true, true>(Vb, nbytes, aoff, xoff, rb, active, As, Bs, acc, kt0,
+                                          kt1);
+        else
+            run_half<TM, BKW, true, false>(Vb, nbytes, aoff, xoff, rb, active, As, Bs, acc, kt0,
+                                           kt1);
+    } else if (vec) {
+        run_tile_flat_body<DT, TM, TM, BKW, true>(Vb, ldb, nbytes, aoff, xoff, b_row0, b_end,
                                                   active, As, Bs, acc, kt0, kt1);
-    else
-        run_tile_flat_body<DT, TM, TN, BKW, false>(Vb, ldb, nbytes, aoff, xoff, b_row0, b_end,
+    } else {
+        run_tile_flat_body<DT, TM, TM, BKW, false>(Vb, ldb, nbytes, aoff, xoff, b_row0, b_end,
                                                    active, As, Bs, acc, kt0, kt1);
+    }
 }
 
 // Block index -> work index so that each XCD receives one contiguous run of
@@ -526,27 +624,26 @@ __device__ __forceinline__ void store_pair(typename Ops<DT>::Acc acc, double si,
 
 // 2-way: the outputs of a lane's micro-tile.  Output (i, j), i < j, at colex
 // j(j-1)/2 + i.
-template <int DT, int TM, int TN>
-__device__ __forceinline__ void epilogue2(const typename Ops<DT>::Acc (&acc)[TM][TN],
-                                          int64_t row0, int64_t col0, int64_t n_v,
-                                          const double* __restrict__ s, float* c2,
+template <int DT, int TM>
+__device__ __forceinline__ void epilogue2(const MicroAcc<DT, TM>& acc, int64_t row0, int64_t col0,
+                                          int64_t n_v, const double* __restrict__ s, float* c2,
                                           void* n2) {
+    using M = Micro<DT, TM>;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int lx = lane % 8, ly = lane / 8;
-    double sc[TN];
+    double sc[M::kC];
 #pragma unroll
-    for (int c = 0; c < TN; ++c) {
-        const int64_t j = col0 + lane_col<TN>(wave, ly, c);
+    for (int c = 0; c < M::kC; ++c) {
+        const int64_t j = col0 + M::col(wave, lane, c);
         sc[c] = j < n_v ? s[j] : 0.0;
     }
 #pragma unroll
-    for (int r = 0; r < TM; ++r) {
-        const int64_t i = row0 + lane_row<TM>(wave, lx, r);
+    for (int r = 0; r < M::kR; ++r) {
+        const int64_t i = row0 + M::row(wave, lane, r);
         if (i >= n_v) continue;
         const double si = s[i];
 #pragma unroll
-        for (int c = 0; c < TN; ++c) {
-            const int64_t j = col0 + lane_col<TN>(wave, ly, c);
+        for (int c = 0; c < M::kC; ++c) {
+            const int64_t j = col0 + M::col(wave, lane, c);
             if (j >= n_v || i >= j) continue;
             store_pair<DT>(acc[r][c], si, sc[c], j * (j - 1) / 2 + i, c2, n2);
         }

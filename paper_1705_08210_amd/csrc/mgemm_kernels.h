@@ -18,18 +18,17 @@ __device__ __forceinline__ bool rows_vec_ok(const void* V, int64_t ld) {
 // symmetry reduction of Section 2.1).
 // ---------------------------------------------------------------------------
 // Raw pair sums of one field chunk, colex order, as 32-bit patterns.
-template <int DT, int TM, int TN>
-__device__ __forceinline__ void store_pairs_raw(const typename Ops<DT>::Acc (&acc)[TM][TN],
-                                                int64_t row0, int64_t col0, int64_t n_v,
-                                                uint32_t* dst) {
+template <int DT, int TM>
+__device__ __forceinline__ void store_pairs_raw(const MicroAcc<DT, TM>& acc, int64_t row0,
+                                                int64_t col0, int64_t n_v, uint32_t* dst) {
+    using M = Micro<DT, TM>;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int lx = lane % 8, ly = lane / 8;
 #pragma unroll
-    for (int r = 0; r < TM; ++r) {
-        const int64_t i = row0 + lane_row<TM>(wave, lx, r);
+    for (int r = 0; r < M::kR; ++r) {
+        const int64_t i = row0 + M::row(wave, lane, r);
 #pragma unroll
-        for (int c = 0; c < TN; ++c) {
-            const int64_t j = col0 + lane_col<TN>(wave, ly, c);
+        for (int c = 0; c < M::kC; ++c) {
+            const int64_t j = col0 + M::col(wave, lane, c);
             if (j >= n_v || i >= j) continue;
             dst[j * (j - 1) / 2 + i] = __builtin_bit_cast(uint32_t, acc[r][c]);
         }
@@ -37,13 +36,12 @@ __device__ __forceinline__ void store_pairs_raw(const typename Ops<DT>::Acc (&ac
 }
 
 template <int DT, int TM, int BKW>
-__global__ __launch_bounds__(kThreads, PS_MIN_WAVES) void ps_mg2_kernel(Mg2Launch a, int64_t ntiles,
+__global__ __launch_bounds__(kThreads, (min_waves<DT, TM, BKW>())) void ps_mg2_kernel(Mg2Launch a, int64_t ntiles,
                                                                       int64_t item0) {
-    using Acc = typename Ops<DT>::Acc;
     constexpr int BM = 16 * TM;
     using Word = typename Ops<DT>::Word;
-    __shared__ __attribute__((aligned(16))) Word As[BKW * (BM + 4)];
-    __shared__ __attribute__((aligned(16))) Word Bs[BKW * (BM + 4)];
+    __shared__ __attribute__((aligned(16))) Word As[TileGeom<DT, TM, BKW>::kLdsWords];
+    __shared__ __attribute__((aligned(16))) Word Bs[TileGeom<DT, TM, BKW>::kLdsWords];
     // work item = (field chunk, tile), chunk-major; item0: this launch's first
     const int64_t w = item0 + xcd_remap(blockIdx.x, gridDim.x);
     if (w >= ntiles * a.nchunks) return;
@@ -62,20 +60,18 @@ __global__ __launch_bounds__(kThreads, PS_MIN_WAVES) void ps_mg2_kernel(Mg2Launc
     const int64_t nbytes = a.n_f * Ops<DT>::kEsz;
     const int64_t kt0 = a.nchunks > 1 ? chunk * a.chunk_tiles : 0;
     const int64_t kt1 = a.nchunks > 1 ? kt0 + a.chunk_tiles : -1;
-    Acc acc[TM][TM];
-    run_tile<DT, TM, TM, BKW, false>((const char*)a.V, ldb, nbytes,
-                                              rows_vec_ok<DT>(a.V, a.ld), row0, a.n_v,
-                                              col0, a.n_v, nullptr, active, As, Bs, acc,
-                                              kt0, kt1);
+    MicroAcc<DT, TM> acc;
+    run_tile<DT, TM, BKW>((const char*)a.V, ldb, nbytes, rows_vec_ok<DT>(a.V, a.ld), row0, a.n_v,
+                          col0, a.n_v, active, As, Bs, acc, kt0, kt1);
     if (!active) return;
     if constexpr (DT != PS_F64) {   // FP64 sums are never split over field chunks
         if (a.nchunks > 1) {
-            store_pairs_raw<DT, TM, TM>(acc, row0, col0, a.n_v,
-                                        (uint32_t*)a.partial + chunk * (a.n_v * (a.n_v - 1) / 2));
+            store_pairs_raw<DT, TM>(acc, row0, col0, a.n_v,
+                                    (uint32_t*)a.partial + chunk * (a.n_v * (a.n_v - 1) / 2));
             return;
         }
     }
-    epilogue2<DT, TM, TM>(acc, row0, col0, a.n_v, a.s, a.c2, a.n2);
+    epilogue2<DT, TM>(acc, row0, col0, a.n_v, a.s, a.c2, a.n2);
 }
 
 // ---------------------------------------------------------------------------
@@ -103,15 +99,15 @@ __global__ __launch_bounds__(kThreads, PS_MIN_WAVES) void ps_mg2_kernel(Mg2Launc
 // stored.  Part 1 of kSlabSplit: row tiles of lex pairs (j, k) against
 // column tiles of i (store_slice_lex).
 template <int DT, int TM>
-__device__ __forceinline__ void store_slice_flat(const typename Ops<DT>::Acc (&acc)[TM][TM],
+__device__ __forceinline__ void store_slice_flat(const MicroAcc<DT, TM>& acc,
                                                  int64_t p0, int64_t pend, int64_t col0,
                                                  const Mg3Launch& a, uint32_t* out) {
+    using M = Micro<DT, TM>;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int lx = lane % 8, ly = lane / 8;
     const int64_t obase = slab_offset(a.n_v, a.j_begin);
 #pragma unroll
-    for (int r = 0; r < TM; ++r) {
-        const int64_t p = p0 + lane_row<TM>(wave, lx, r);
+    for (int r = 0; r < M::kR; ++r) {
+        const int64_t p = p0 + M::row(wave, lane, r);
         if (p >= pend) continue;
         const int64_t j = pair_j(p);
         const int64_t i = p - j * (j - 1) / 2;
@@ -120,8 +116,8 @@ __device__ __forceinline__ void store_slice_flat(const typename Ops<DT>::Acc (&a
         int32_t nij = 0;   // the staged pair (i, j), colex index p
         if constexpr (DT == PS_U8) nij = ((const int32_t*)a.n2)[p];
 #pragma unroll
-        for (int c = 0; c < TM; ++c) {
-            const int64_t k = col0 + lane_col<TM>(wave, ly, c);
+        for (int c = 0; c < M::kC; ++c) {
+            const int64_t k = col0 + M::col(wave, lane, c);
             if (k >= a.n_v || k <= j) continue;
             if constexpr (DT == PS_F64)
                 ((double*)out)[base + k * j] = acc[r][c];
@@ -137,15 +133,15 @@ __device__ __forceinline__ void store_slice_flat(const typename Ops<DT>::Acc (&a
 // its A operand row min(v_j, v_k); columns are i from col0; entries with
 // i >= j are computed by waves that also hold wanted ones and never stored.
 template <int DT, int TM>
-__device__ __forceinline__ void store_slice_lex(const typename Ops<DT>::Acc (&acc)[TM][TM],
+__device__ __forceinline__ void store_slice_lex(const MicroAcc<DT, TM>& acc,
                                                 int64_t q0, int64_t qend, int64_t col0,
                                                 const Mg3Launch& a, uint32_t* out) {
+    using M = Micro<DT, TM>;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int lx = lane % 8, ly = lane / 8;
     const int64_t obase = slab_offset(a.n_v, a.j_begin);
 #pragma unroll
-    for (int r = 0; r < TM; ++r) {
-        const int64_t q = q0 + lane_row<TM>(wave, lx, r);
+    for (int r = 0; r < M::kR; ++r) {
+        const int64_t q = q0 + M::row(wave, lane, r);
         if (q >= qend) continue;
         int64_t j, k;
         lex_pair(a.n_v, q, j, k);
@@ -154,8 +150,8 @@ __device__ __forceinline__ void store_slice_lex(const typename Ops<DT>::Acc (&ac
         int32_t njk = 0;   // the staged pair (j, k)
         if constexpr (DT == PS_U8) njk = ((const int32_t*)a.n2)[k * (k - 1) / 2 + j];
 #pragma unroll
-        for (int c = 0; c < TM; ++c) {
-            const int64_t i = col0 + lane_col<TM>(wave, ly, c);
+        for (int c = 0; c < M::kC; ++c) {
+            const int64_t i = col0 + M::col(wave, lane, c);
             if (i >= j) continue;
             if constexpr (DT == PS_F64)
                 ((double*)out)[base + i] = acc[r][c];
@@ -168,14 +164,13 @@ __device__ __forceinline__ void store_slice_lex(const typename Ops<DT>::Acc (&ac
 }
 
 template <int DT, int TM, int BKW>
-__global__ __launch_bounds__(kThreads, PS_MIN_WAVES) void ps_mg3f_kernel(Mg3Launch a,
+__global__ __launch_bounds__(kThreads, (min_waves<DT, TM, BKW>())) void ps_mg3f_kernel(Mg3Launch a,
                                                                        int64_t item0) {
-    using Acc = typename Ops<DT>::Acc;
     constexpr int BM = 16 * TM;
     using Word = typename Ops<DT>::Word;
-    using SA = Stager<BM, BKW, Word>;
-    __shared__ __attribute__((aligned(16))) Word As[BKW * (BM + 4)];
-    __shared__ __attribute__((aligned(16))) Word Bs[BKW * (BM + 4)];
+    using SA = TileGeom<DT, TM, BKW>;
+    __shared__ __attribute__((aligned(16))) Word As[TileGeom<DT, TM, BKW>::kLdsWords];
+    __shared__ __attribute__((aligned(16))) Word Bs[TileGeom<DT, TM, BKW>::kLdsWords];
     const int64_t w = item0 + xcd_remap(blockIdx.x, gridDim.x);
     if (w >= a.ntiles * a.nchunks) return;
     const int64_t chunk = w / a.ntiles, tw = w % a.ntiles;
@@ -221,22 +216,24 @@ __global__ __launch_bounds__(kThreads, PS_MIN_WAVES) void ps_mg3f_kernel(Mg3Laun
     int64_t aoff[SA::kCh], xoff[SA::kCh];
 #pragma unroll
     for (int c = 0; c < SA::kCh; ++c) {
-        const int64_t r = r0 + (threadIdx.x + c * kThreads) % BM;
+        const int64_t r = r0 + SA::row(c);
         if (!lexp) {
-            const int64_t j = r < rend ? pair_j(r) : 0;
-            aoff[c] = r < rend ? (r - j * (j - 1) / 2) * ldb : -1;
+            const bool in = r < rend || DT == PS_F16;   // FP16: a valid pair past the end
+            const int64_t p = r < rend ? r : rend - 1;
+            const int64_t j = in ? pair_j(p) : 0;
+            aoff[c] = in ? (p - j * (j - 1) / 2) * ldb : -1;
             xoff[c] = j * ldb;
         } else {
             int64_t j, k;
             lex_pair(a.n_v, r < rend ? r : rend - 1, j, k);
-            aoff[c] = r < rend ? j * ldb : -1;
+            aoff[c] = r < rend || DT == PS_F16 ? j * ldb : -1;
             xoff[c] = k * ldb;
         }
     }
-    Acc acc[TM][TM];
+    MicroAcc<DT, TM> acc;
     const int64_t kt0 = a.nchunks > 1 ? chunk * a.chunk_tiles : 0;
     const int64_t kt1 = a.nchunks > 1 ? kt0 + a.chunk_tiles : -1;
-    run_tile_flat<DT, TM, TM, BKW>((const char*)a.V, ldb, nbytes, rows_vec_ok<DT>(a.V, a.ld),
+    run_tile_flat<DT, TM, BKW>((const char*)a.V, ldb, nbytes, rows_vec_ok<DT>(a.V, a.ld),
                                    aoff, xoff, col0, a.n_v, active, As, Bs, acc, kt0, kt1);
     if (active) {
         uint32_t* dst = DT == PS_F64 ? (uint32_t*)a.partial   // stage doubles, never split
@@ -351,13 +348,12 @@ hipError_t go_c3_finish(const Mg3Launch& a, hipStream_t st) {
 // instead of 4 waves per SIMD).
 // ---------------------------------------------------------------------------
 template <int DT, int TM, int BKW>
-__global__ __launch_bounds__(kThreads, PS_MIN_WAVES) void ps_mgb_kernel(MgBatchLaunch a,
+__global__ __launch_bounds__(kThreads, (min_waves<DT, TM, BKW>())) void ps_mgb_kernel(MgBatchLaunch a,
                                                                       int64_t item0) {
-    using Acc = typename Ops<DT>::Acc;
     constexpr int BM = 16 * TM;
     using Word = typename Ops<DT>::Word;
-    __shared__ __attribute__((aligned(16))) Word As[BKW * (BM + 4)];
-    __shared__ __attribute__((aligned(16))) Word Bs[BKW * (BM + 4)];
+    __shared__ __attribute__((aligned(16))) Word As[TileGeom<DT, TM, BKW>::kLdsWords];
+    __shared__ __attribute__((aligned(16))) Word Bs[TileGeom<DT, TM, BKW>::kLdsWords];
     // block b runs on XCD b % kXcds: its position b / kXcds in that XCD's list
     const int64_t b = item0 + blockIdx.x;
     const int x = (int)(b % kXcds);
@@ -374,15 +370,15 @@ __global__ __launch_bounds__(kThreads, PS_MIN_WAVES) void ps_mgb_kernel(MgBatchL
     const bool active = r_lo < p.n_v && c_lo < p.n_v && r_lo + 1 < c_hi;
     const int64_t kt0 = p.nchunks > 1 ? (int64_t)bt.chunk * a.chunk_tiles : 0;
     const int64_t kt1 = p.nchunks > 1 ? kt0 + a.chunk_tiles : -1;
-    Acc acc[TM][TM];
-    run_tile<DT, TM, TM, BKW, false>((const char*)p.V, p.ld * Ops<DT>::kEsz,
-                                     p.n_f * Ops<DT>::kEsz, rows_vec_ok<DT>(p.V, p.ld), row0,
-                                     p.n_v, col0, p.n_v, nullptr, active, As, Bs, acc, kt0, kt1);
+    MicroAcc<DT, TM> acc;
+    run_tile<DT, TM, BKW>((const char*)p.V, p.ld * Ops<DT>::kEsz, p.n_f * Ops<DT>::kEsz,
+                          rows_vec_ok<DT>(p.V, p.ld), row0, p.n_v, col0, p.n_v, active, As, Bs, acc,
+                          kt0, kt1);
     // raw sums only: ps_finish2_batched_kernel forms n2 and c2 of every problem
     if (active)
-        store_pairs_raw<DT, TM, TM>(acc, row0, col0, p.n_v,
-                                    (uint32_t*)p.partial +
-                                        (int64_t)bt.chunk * (p.n_v * (p.n_v - 1) / 2));
+        store_pairs_raw<DT, TM>(acc, row0, col0, p.n_v,
+                                (uint32_t*)p.partial +
+                                    (int64_t)bt.chunk * (p.n_v * (p.n_v - 1) / 2));
 }
 
 // ---------------------------------------------------------------------------
