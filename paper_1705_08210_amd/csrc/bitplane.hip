@@ -236,16 +236,23 @@ __device__ __forceinline__ void bp_sync(int64_t s, int64_t ns) {
 // ssj: s_j of the tile's rows.  F32: 2 n2 and s_i + s_j are integers below
 // 2^24, and the FP32 quotient is the FP64 quotient's rounding (div_u24);
 // otherwise FP64.  INNER: every i < j < n_v in the block.
-template <int WM, int WN, bool F32, bool INNER, typename R>
+// One of the two outputs at a time and no branch inside a full block: with a
+// branch per element around either store each quotient ran as a serial chain
+// (8192 x 32768, three levels, 4.31 -> 4.17 ms; 8190 x 20001 binary 0.666 -> 0.656;
+// 400 x 6000, two levels, 34 -> 30 us; 400 x 20001 binary, bound by the stores,
+// 210 -> 218 us).
+template <int WM, int WN, bool F32, bool INNER, bool C2, typename R>
 __device__ __forceinline__ void bp_store2(const LvArgs& a, const v16f_t (&acc)[WM][WN], int64_t i0,
                                           int64_t jw, int wr, const R* ssj) {
     const int lane = threadIdx.x % 64;
     const int64_t i = i0 + lane % 32;
     R si[WN];
+    if constexpr (C2) {
 #pragma unroll
-    for (int n = 0; n < WN; ++n) {
-        const int64_t ii = i + n * 32;
-        si[n] = (R)a.s[INNER || ii < a.n_v ? ii : a.n_v - 1];
+        for (int n = 0; n < WN; ++n) {
+            const int64_t ii = i + n * 32;
+            si[n] = (R)a.s[INNER || ii < a.n_v ? ii : a.n_v - 1];
+        }
     }
 #pragma unroll
     for (int m = 0; m < WM; ++m)
@@ -256,21 +263,27 @@ __device__ __forceinline__ void bp_store2(const LvArgs& a, const v16f_t (&acc)[W
             int64_t row = j * (j - 1) / 2 + i;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const R sj = ssj[wr + dr + e];
+                float c[WN];
+                if constexpr (C2) {
+                    const R sj = ssj[wr + dr + e];
+#pragma unroll
+                    for (int n = 0; n < WN; ++n) {
+                        const float num = acc[m][n][g * 4 + e];
+                        const R d = si[n] + sj;
+                        if constexpr (F32)
+                            c[n] = div_u24(2.0f * num, d > 0.0f ? d : 1.0f);
+                        else
+                            c[n] = (float)((2.0 * (double)num) / (d > 0.0 ? d : 1.0));
+                        c[n] = d > (R)0 ? c[n] : 0.0f;
+                    }
+                }
 #pragma unroll
                 for (int n = 0; n < WN; ++n) {
                     if (!INNER && (j + e >= a.n_v || i + n * 32 >= j + e)) continue;
-                    const float num = acc[m][n][g * 4 + e];
-                    if (a.n2) a.n2[row + n * 32] = (int32_t)num;
-                    if (a.c2) {
-                        const R d = si[n] + sj;
-                        float c;
-                        if constexpr (F32)
-                            c = div_u24(2.0f * num, d > 0.0f ? d : 1.0f);
-                        else
-                            c = (float)((2.0 * (double)num) / (d > 0.0 ? d : 1.0));
-                        a.c2[row + n * 32] = d > (R)0 ? c : 0.0f;
-                    }
+                    if constexpr (C2)
+                        a.c2[row + n * 32] = c[n];
+                    else
+                        a.n2[row + n * 32] = (int32_t)acc[m][n][g * 4 + e];
                 }
                 row += j + e;
             }
@@ -287,10 +300,19 @@ __device__ __forceinline__ void bp_epilogue2(const LvArgs& a, const v16f_t (&acc
     __syncthreads();
     if (!active) return;
     const int64_t iw = i0 + wc, jw = j0 + wr;
-    if (iw + 32 * WN <= jw && jw + 32 * WM <= a.n_v)
-        bp_store2<WM, WN, F32, true, R>(a, acc, iw, jw, wr, ssj);
-    else
-        bp_store2<WM, WN, F32, false, R>(a, acc, iw, jw, wr, ssj);
+    const bool inner = iw + 32 * WN <= jw && jw + 32 * WM <= a.n_v;
+    if (a.c2) {
+        if (inner)
+            bp_store2<WM, WN, F32, true, true, R>(a, acc, iw, jw, wr, ssj);
+        else
+            bp_store2<WM, WN, F32, false, true, R>(a, acc, iw, jw, wr, ssj);
+    }
+    if (a.n2) {
+        if (inner)
+            bp_store2<WM, WN, F32, true, false, R>(a, acc, iw, jw, wr, ssj);
+        else
+            bp_store2<WM, WN, F32, false, false, R>(a, acc, iw, jw, wr, ssj);
+    }
 }
 
 template <int WM, int WN, int S>
