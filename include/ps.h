@@ -95,10 +95,10 @@ typedef enum {
 
 /* Compute path for the pair numerators. */
 typedef enum {
-    PS_PATH_AUTO = 0,    /* U8 with 1 <= levels <= 15: MFMA_FP4 (triangles of
-                            more than 1024 vectors and the 3-way slices), MFMA
-                            where that does not apply, each within its limits
-                            below; otherwise VALU */
+    PS_PATH_AUTO = 0,    /* U8 with 1 <= levels <= 15: MFMA_FP4 for triangles of
+                            more than 1024 vectors and the 3-way slices, MFMA
+                            where that cannot take the shape, each within its
+                            limits below; otherwise VALU */
     PS_PATH_VALU = 1,    /* register-blocked min/add on the vector ALUs */
     PS_PATH_MFMA = 2,    /* alias PS_PATH_MFMA_THERMO.  U8 only:
                             min(a,b) = sum_{t=1..levels} [a>=t][b>=t], an

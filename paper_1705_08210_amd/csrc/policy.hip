@@ -158,7 +158,11 @@ static bool mfma_can(int path, int way, int64_t n_f, int64_t n_v, int levels, in
     return (int64_t)levels * n_f < ((int64_t)1 << 31) && mfma_row_fits(n_f, levels, 0);
 }
 
-// AUTO keeps triangles of up to this many vectors on the paths without a plane workspace.
+// AUTO keeps triangles of up to this many vectors on a path without a plane
+// workspace: the VALU path with its small tiles (256-row matrix-core tiles leave
+// most of the chip idle: three levels, int8 / VALU, us: 4096 fields, 512 vectors
+// 115 / 24; 12000 fields, 1024 vectors 220 / 117), int8 only where the byte
+// sums do not fit 32 bits.
 static constexpr int64_t kBpMinVectors = 1024;
 
 // A tuned entry for (dt, way, path) covering the shape, or -1.
@@ -182,6 +186,7 @@ int choose_path(int32_t dt, const ps_opts* o, int way, int64_t n_f, int64_t n_v,
     if ((t == PS_PATH_MFMA || t == PS_PATH_MFMA_FP4) &&
         mfma_can(t, way, n_f, n_v, o->levels, wide, ld))
         return t;
+    if (way == 2 && n_v <= kBpMinVectors && 255 * n_f < ((int64_t)1 << 31)) return PS_PATH_VALU;
     if (mfma_can(PS_PATH_MFMA_FP4, way, n_f, n_v, o->levels, wide, ld) &&
         (way == 2 ? n_v > kBpMinVectors : bp3_fits(n_f, n_v, o->levels)))
         return PS_PATH_MFMA_FP4;

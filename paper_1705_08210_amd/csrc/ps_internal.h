@@ -284,8 +284,8 @@ Split plan_split(int32_t dt, int64_t n_f, int64_t n_v, int cfg, const ps_opts* o
 bool is_mfma(int path);
 // AUTO for PS_U8 data with 1 <= levels <= 15: the path a tuned entry
 // (dtype, way, PS_PATH_AUTO) registers for the shape, when that path can
-// take it; else the FP4 path (planes of bits) for triangles of more than
-// kBpMinVectors vectors and for the 3-way slices when it can take the shape;
+// take it; else the VALU path for triangles of up to kBpMinVectors vectors, the
+// FP4 path (planes of bits) for larger ones and the 3-way slices when it can;
 // else the int8 MFMA path when its rows fit the 32-bit tile offsets
 // (mfma_ld_fits on the fused path, mfma_row_fits on planes); else VALU.  ld
 // is the row stride (n_f in size queries).
