@@ -75,7 +75,7 @@ hipError_t dispatch(int cfg, Go go) {
 
 // a.V is the packed matrix, a.n_f its words per row in use, a.ld its row
 // length in words.
-hipError_t launch_mg2_b1(const Mg2Launch& a, hipStream_t st) {
+hipError_t launch_mg2_b1(const Mg2Call& a, hipStream_t st) {
     return dispatch(a.cfg, [&](auto tm, auto bkw) {
         return go_mg2<PS_B1, decltype(tm)::value, decltype(bkw)::value>(a, st);
     });

@@ -19,7 +19,7 @@ hipError_t dispatch(int cfg, Go go) {
 }
 }  // namespace
 
-hipError_t launch_mg2_u8(const Mg2Launch& a, hipStream_t st) {
+hipError_t launch_mg2_u8(const Mg2Call& a, hipStream_t st) {
     return dispatch(a.cfg, [&](auto tm, auto bkw) {
         return go_mg2<PS_U8, decltype(tm)::value, decltype(bkw)::value>(a, st);
     });

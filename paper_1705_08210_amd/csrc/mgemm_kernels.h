@@ -386,13 +386,13 @@ __global__ __launch_bounds__(kThreads, (min_waves<DT, TM, BKW>())) void ps_mgb_k
 // ---------------------------------------------------------------------------
 
 template <int DT, int TM, int BKW>
-hipError_t go_mg2(const Mg2Launch& a, hipStream_t st) {
+hipError_t go_mg2(const Mg2Call& a, hipStream_t st) {
     if (a.small) return go_sm2<DT>(a, st);
     const int64_t T = shard_tiles(tri_tiles(a.n_v, 16 * TM), a.shard0, a.nshards);
     if (T == 0) return hipSuccess;
     return launch_items(T * a.nchunks, kThreads, kXcds, [&](unsigned grid, int64_t item0) {
-        hipLaunchKernelGGL((ps_mg2_kernel<DT, TM, BKW>), dim3(grid), dim3(kThreads), 0, st, a,
-                           T, item0);
+        hipLaunchKernelGGL((ps_mg2_kernel<DT, TM, BKW>), dim3(grid), dim3(kThreads), 0, st,
+                           static_cast<const Mg2Launch&>(a), T, item0);
     });
 }
 

@@ -179,7 +179,8 @@ __device__ __forceinline__ void sm_range(int64_t nbytes, int32_t nchunks, int64_
 // with a.s_out, blocks of NW vectors to sum (nothing in this launch reads
 // the sums then: raw chunk sums, or numerators alone).
 template <int DT, int NW, bool VEC>
-__global__ __launch_bounds__(64 * NW, 2) void ps_sm2_kernel(Mg2Launch a, int64_t ntiles, int64_t item0) {
+__global__ __launch_bounds__(64 * NW, 2) void ps_sm2_kernel(Mg2Call a, int64_t ntiles,
+                                                             int64_t item0) {
     using Word = typename Ops<DT>::Word;
     using Acc = typename Ops<DT>::Acc;
     constexpr int ESZ = Ops<DT>::kEsz;
@@ -358,7 +359,7 @@ hipError_t sm_dispatch(const void* V, int64_t ld, int waves, Go go) {
 }
 
 template <int DT>
-hipError_t go_sm2(const Mg2Launch& a, hipStream_t st) {
+hipError_t go_sm2(const Mg2Call& a, hipStream_t st) {
     const int64_t T = tri_tiles(a.n_v, kSmB);
     return sm_dispatch<DT>(a.V, a.ld, a.small, [&](auto nw, auto vec) {
         constexpr int NW = decltype(nw)::value;

@@ -79,7 +79,7 @@ struct Carver {
     }
 };
 
-static hipError_t launch_mg2(int32_t dt, const Mg2Launch& a, hipStream_t st) {
+static hipError_t launch_mg2(int32_t dt, const Mg2Call& a, hipStream_t st) {
     switch (dt) {
     case PS_F32: return launch_mg2_f32(a, st);
     case PS_F16: return launch_mg2_f16(a, st);
@@ -308,13 +308,13 @@ static ps_status ps2_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
         const int64_t W = bits_row_words(n_f);
         e = launch_pack_bits((const uint8_t*)V, n_f, n_v, ld, (uint32_t*)planes, stream);
         if (e != hipSuccess) return hip_fail(e, "bit packing launch");
-        Mg2Launch a{planes, W, n_v, W, s, c2, n2, cfg, 1, 0, nullptr, shard, nshards};
+        Mg2Call a{{planes, W, n_v, W, s, c2, n2, cfg, 1, 0, nullptr, shard, nshards}, 0, nullptr};
         e = launch_mg2(PS_B1, a, stream);
         return e == hipSuccess ? PS_OK : hip_fail(e, "2-way bits launch");
     }
-    Mg2Launch a{V,         n_f,           n_v,     ld,    s,       c2,    n2,
-                cfg,       sp.nchunks,    sp.chunk_tiles, partial, shard, nshards,
-                small,     with_sums ? s_ws : nullptr};
+    Mg2Call a{{V, n_f, n_v, ld, s, c2, n2, cfg, sp.nchunks, sp.chunk_tiles, partial, shard,
+               nshards},
+              small, with_sums ? s_ws : nullptr};
     e = launch_mg2(dtype, a, stream);
     if (e == hipSuccess && sp.nchunks > 1) e = launch_finish2(dtype, a, stream);
     return e == hipSuccess ? PS_OK : hip_fail(e, "2-way launch");
@@ -635,8 +635,9 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
         kn_f = kld = bits_row_words(n_f);
     }
     if (!n2) {  // the pair numerators of Eq. 1 (the 2-way mGEMM prepass)
-        Mg2Launch a{KV,      kn_f, n_v, kld, s, nullptr, n2_ws, cfg2, sp2.nchunks, sp2.chunk_tiles,
-                    partial, 0,    1,   pair_small, with_sums ? s_ws : nullptr};
+        Mg2Call a{{KV, kn_f, n_v, kld, s, nullptr, n2_ws, cfg2, sp2.nchunks, sp2.chunk_tiles,
+                   partial, 0, 1},
+                  pair_small, with_sums ? s_ws : nullptr};
         e = launch_mg2(kdt, a, stream);
         if (e == hipSuccess && sp2.nchunks > 1) e = launch_finish2(dtype, a, stream);
         if (e != hipSuccess) return hip_fail(e, "3-way numerator prepass launch");

@@ -317,8 +317,11 @@ struct Mg2Launch {
     // tile shard: only the tiles t = shard0 + u * nshards of the upper
     // triangle (nshards <= 1: all tiles)
     int64_t shard0, nshards;
-    // small: waves of the 32 x 32 tiles of mgemm_small.h instead of cfg's 64 x 64
-    // (same chunks), or 0; s_out: the launch also writes the per-vector sums there
+};
+
+// small: waves of the 32 x 32 tiles of mgemm_small.h instead of cfg's 64 x 64
+// (same chunks), or 0; s_out: the launch also writes the per-vector sums there.
+struct Mg2Call : Mg2Launch {
     int32_t small;
     double* s_out;
 };
@@ -405,14 +408,14 @@ int64_t slab_tiles(int64_t n_v, int64_t jb, int64_t je, int bm, int mode, int ob
 // Launchers (one per storage type; defined in the per-type units).
 hipError_t launch_sums(const void* V, int32_t dt, int64_t n_f, int64_t n_v,
                        int64_t ld, double* s, int32_t* bad, hipStream_t st);
-hipError_t launch_mg2_f32(const Mg2Launch& a, hipStream_t st);
-hipError_t launch_mg2_f16(const Mg2Launch& a, hipStream_t st);
-hipError_t launch_mg2_u8(const Mg2Launch& a, hipStream_t st);
+hipError_t launch_mg2_f32(const Mg2Call& a, hipStream_t st);
+hipError_t launch_mg2_f16(const Mg2Call& a, hipStream_t st);
+hipError_t launch_mg2_u8(const Mg2Call& a, hipStream_t st);
 hipError_t launch_mg3_f32(const Mg3Launch& a, hipStream_t st);
 hipError_t launch_mg3_f16(const Mg3Launch& a, hipStream_t st);
 hipError_t launch_mg3_u8(const Mg3Launch& a, hipStream_t st);
-hipError_t launch_mg2_b1(const Mg2Launch& a, hipStream_t st);
-hipError_t launch_mg2_f64(const Mg2Launch& a, hipStream_t st);
+hipError_t launch_mg2_b1(const Mg2Call& a, hipStream_t st);
+hipError_t launch_mg2_f64(const Mg2Call& a, hipStream_t st);
 hipError_t launch_mg3_f64(const Mg3Launch& a, hipStream_t st);
 hipError_t launch_mg3_b1(const Mg3Launch& a, hipStream_t st);
 // V (uint8 0/1, n_v rows of ld bytes, n_f fields) -> P (n_v rows of
