@@ -278,8 +278,12 @@ __device__ __forceinline__ int lane_col(int wave, int ly, int c) {
 // Waves per SIMD a tile kernel is compiled for.  The FP16 128 x 128 tiles with
 // 16-word field tiles fit three (168 registers) with their chunk loop rolled:
 // 15.70 -> 15.41 ms (20000 x 8191 2-way), 18.60 -> 18.25 ms (4096 x 1024 3-way).
+// The FP32 64 x 64 tiles fit six (80 registers): left alone the slices take 78 or
+// 127 and the batch 72 or 116, as small changes have it.
 template <int DT, int TM, int BKW>
-constexpr int min_waves() { return DT == PS_F16 && TM == 8 && BKW == 16 ? 3 : PS_MIN_WAVES; }
+constexpr int min_waves() {
+    return DT == PS_F16 && TM == 8 && BKW == 16 ? 3 : DT == PS_F32 && TM == 4 ? 6 : PS_MIN_WAVES;
+}
 
 // The outputs a lane holds: kR x kC elements, (r, c) at tile row row(r), column
 // col(c).
@@ -569,6 +573,34 @@ __device__ __forceinline__ void run_tile_flat(
 __device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t grid) {
     const int64_t per = grid / kXcds;
     return (b % kXcds) * per + b / kXcds;
+}
+
+// Work index (xcd_remap) -> field chunk and tile; false: no work.  Split sums of
+// many tiles: an XCD's run is its eighth of the tiles, chunk after chunk, so that
+// the shorter last chunk ends every XCD's run.  (A run of the chunk-major list
+// of all tiles gave some XCDs short chunks alone: 4500 fields took as long as
+// 8000.)  FP32, ms, chunk-major / so: 2-way 4500 fields x 4200 vectors 2.75 / 1.58,
+// 5000 x 9001 11.7 / 7.55, 20000 x 16384 87.4 / 82.3; 3-way 5000 x 1024 50.4 / 30.9.
+// Few tiles do not deal out evenly, and a small triangle is split into more, even
+// chunks anyway: the chunk-major list.
+inline constexpr int64_t kXcdTiles = 256;
+__host__ __device__ inline int64_t chunk_items(int64_t ntiles, int32_t nchunks) {
+    return nchunks > 1 && ntiles >= kXcdTiles ? (ntiles + kXcds - 1) / kXcds * kXcds * nchunks
+                                              : ntiles * nchunks;
+}
+__device__ __forceinline__ bool chunk_decode(int64_t w, int64_t ntiles, int32_t nchunks,
+                                             int64_t& chunk, int64_t& t) {
+    if (w >= chunk_items(ntiles, nchunks)) return false;
+    if (nchunks > 1 && ntiles >= kXcdTiles) {
+        const int64_t per = (ntiles + kXcds - 1) / kXcds, run = per * nchunks;
+        const int64_t x = w / run, r = w - x * run;
+        chunk = r / per;
+        t = x * per + (r - chunk * per);
+        return t < ntiles;
+    }
+    chunk = w / ntiles;
+    t = w - chunk * ntiles;
+    return true;
 }
 
 // Upper-triangle tile t (column-major: (0,0), (0,1), (1,1), (0,2), ...).

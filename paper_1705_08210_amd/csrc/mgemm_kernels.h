@@ -42,11 +42,10 @@ __global__ __launch_bounds__(kThreads, (min_waves<DT, TM, BKW>())) void ps_mg2_k
     using Word = typename Ops<DT>::Word;
     __shared__ __attribute__((aligned(16))) Word As[TileGeom<DT, TM, BKW>::kLdsWords];
     __shared__ __attribute__((aligned(16))) Word Bs[TileGeom<DT, TM, BKW>::kLdsWords];
-    // work item = (field chunk, tile), chunk-major; item0: this launch's first
-    const int64_t w = item0 + xcd_remap(blockIdx.x, gridDim.x);
-    if (w >= ntiles * a.nchunks) return;
-    const int64_t chunk = w / ntiles;
-    const int64_t t = a.nshards > 1 ? a.shard0 + (w % ntiles) * a.nshards : w % ntiles;
+    // work item = (field chunk, tile); item0: this launch's first
+    int64_t chunk, t;
+    if (!chunk_decode(item0 + xcd_remap(blockIdx.x, gridDim.x), ntiles, a.nchunks, chunk, t)) return;
+    if (a.nshards > 1) t = a.shard0 + t * a.nshards;
     int64_t bi, bj;
     tri_decode(t, bi, bj);   // column-major: measured faster here than grouped order
     const int64_t row0 = bi * BM, col0 = bj * BM;
@@ -171,9 +170,9 @@ __global__ __launch_bounds__(kThreads, (min_waves<DT, TM, BKW>())) void ps_mg3f_
     using SA = TileGeom<DT, TM, BKW>;
     __shared__ __attribute__((aligned(16))) Word As[TileGeom<DT, TM, BKW>::kLdsWords];
     __shared__ __attribute__((aligned(16))) Word Bs[TileGeom<DT, TM, BKW>::kLdsWords];
-    const int64_t w = item0 + xcd_remap(blockIdx.x, gridDim.x);
-    if (w >= a.ntiles * a.nchunks) return;
-    const int64_t chunk = w / a.ntiles, tw = w % a.ntiles;
+    int64_t chunk, tw;
+    if (!chunk_decode(item0 + xcd_remap(blockIdx.x, gridDim.x), a.ntiles, a.nchunks, chunk, tw))
+        return;
     // kSlabSplit: tiles past ntiles0 are the lex-ordered part's
     const bool split = a.mode == kSlabSplit;
     const bool lexp = split && tw >= a.ntiles0;
@@ -390,7 +389,7 @@ hipError_t go_mg2(const Mg2Call& a, hipStream_t st) {
     if (a.small) return go_sm2<DT>(a, st);
     const int64_t T = shard_tiles(tri_tiles(a.n_v, 16 * TM), a.shard0, a.nshards);
     if (T == 0) return hipSuccess;
-    return launch_items(T * a.nchunks, kThreads, kXcds, [&](unsigned grid, int64_t item0) {
+    return launch_items(chunk_items(T, a.nchunks), kThreads, kXcds, [&](unsigned grid, int64_t item0) {
         hipLaunchKernelGGL((ps_mg2_kernel<DT, TM, BKW>), dim3(grid), dim3(kThreads), 0, st,
                            static_cast<const Mg2Launch&>(a), T, item0);
     });
@@ -400,7 +399,7 @@ template <int DT, int TM, int BKW>
 hipError_t go_mg3(const Mg3Launch& a, hipStream_t st) {
     if (a.ntiles == 0) return hipSuccess;
     if (a.mode != kSlabFlat && a.mode != kSlabSplit) return hipErrorInvalidValue;
-    return launch_items(a.ntiles * a.nchunks, kThreads, kXcds, [&](unsigned grid, int64_t item0) {
+    return launch_items(chunk_items(a.ntiles, a.nchunks), kThreads, kXcds, [&](unsigned grid, int64_t item0) {
         hipLaunchKernelGGL((ps_mg3f_kernel<DT, TM, BKW>), dim3(grid), dim3(kThreads), 0, st, a,
                            item0);
     });
