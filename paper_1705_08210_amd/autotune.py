@@ -31,15 +31,17 @@ from . import ps
 
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tune_cache.json")
 
-# bucket edges: [lo, hi)
-NF_BUCKETS = [(0, 2048), (2048, 8192), (8192, 1 << 40)]
-NV_BUCKETS = [(0, 1024), (1024, 4096), (4096, 1 << 40)]
+# bucket edges: [lo, hi); the last of each lies inside the others (a later entry wins):
+# two field chunks of many vectors, where every tile splits the fields alike
+NF_BUCKETS = [(0, 2048), (2048, 8192), (8192, 1 << 40), (4097, 8192)]
+NV_BUCKETS = [(0, 1024), (1024, 4096), (4096, 1 << 40), (6000, 1 << 40)]
 # representative shapes per bucket (n_f, n_v) -- a tile choice depends on
 # how many tiles fill the chip and on the depth of the field loop
 REPS = {
     2: {(0, 0): (1024, 512), (0, 1): (1024, 2048), (0, 2): (1024, 8192),
         (1, 0): (4096, 512), (1, 1): (4096, 2048), (1, 2): (4096, 8192),
-        (2, 0): (16384, 512), (2, 1): (16384, 2048), (2, 2): (16384, 8192)},
+        (2, 0): (16384, 512), (2, 1): (16384, 2048), (2, 2): (16384, 8192),
+        (3, 3): (6000, 12000)},
     3: {(0, 0): (1024, 256), (1, 0): (4096, 384), (2, 0): (12000, 256),
         (0, 1): (1024, 1024), (1, 1): (4096, 1024), (2, 1): (12000, 1024)},
 }
