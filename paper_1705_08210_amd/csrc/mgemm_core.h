@@ -278,11 +278,12 @@ __device__ __forceinline__ int lane_col(int wave, int ly, int c) {
 // Waves per SIMD a tile kernel is compiled for.  The FP16 128 x 128 tiles with
 // 16-word field tiles fit three (168 registers) with their chunk loop rolled:
 // 15.70 -> 15.41 ms (20000 x 8191 2-way), 18.60 -> 18.25 ms (4096 x 1024 3-way).
-// The FP32 64 x 64 tiles fit six (80 registers): left alone the slices take 78 or
-// 127 and the batch 72 or 116, as small changes have it.
+// The FP32 64 x 64 tiles: asked for five they take 63 to 76 registers (six and more
+// waves); left alone the slices took 78 or 127 and the batch 72 or 116 as small
+// changes had it, asked for six the slices spill one (3-way 4096 x 500 3.73 -> 3.69 ms).
 template <int DT, int TM, int BKW>
 constexpr int min_waves() {
-    return DT == PS_F16 && TM == 8 && BKW == 16 ? 3 : DT == PS_F32 && TM == 4 ? 6 : PS_MIN_WAVES;
+    return DT == PS_F16 && TM == 8 && BKW == 16 ? 3 : DT == PS_F32 && TM == 4 ? 5 : PS_MIN_WAVES;
 }
 
 // The outputs a lane holds: kR x kC elements, (r, c) at tile row row(r), column
