@@ -599,7 +599,7 @@ __device__ __forceinline__ bool chunk_decode(int64_t w, int64_t ntiles, int32_t 
         t = x * per + (r - chunk * per);
         return t < ntiles;
     }
-    chunk = w / ntiles;
+    chunk = nchunks > 1 ? w / ntiles : 0;
     t = w - chunk * ntiles;
     return true;
 }
