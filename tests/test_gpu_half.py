@@ -4,6 +4,8 @@ with rows of any alignment, against the oracle on the FP16 values (at most 4200
 terms, FP32 sums: 1e-5); and a vector with infinities and NaN, which must not
 touch the pairs of the others."""
 
+import itertools
+
 import numpy as np
 import pytest
 
@@ -66,3 +68,34 @@ def test_non_finite_vector_leaves_the_others(tile):
     others = ~(np.isin(i, (70, 90)) | np.isin(j, (70, 90)))
     idx = colex(i[others], j[others])
     assert np.array_equal(got[idx].view(np.uint32), clean[idx].view(np.uint32))
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3])
+def test_infinities_of_either_sign_leave_the_others(tile):
+    """Out-of-domain vectors as rows and as columns of a tile, and inside it:
+    2-way, batched and 3-way outputs of the other vectors keep their bits."""
+    from paper_1705_08210_amd import ps
+    from psx import jslab
+    bad = (0, 70, 149)
+    V = _half(150, 300, seed=9)
+    W = V.copy()
+    for v in bad:
+        W[v, 10:20] = -np.inf
+        W[v, 25] = np.inf
+        W[v, 30] = np.nan
+        W[v, 40] = -1.0
+    W[70] = -np.inf
+    announce(f"half infinities tile={tile}")
+    Vd, Wd = to_dev(V), to_dev(W)
+    i, j = np.triu_indices(150, 1)
+    ok = ~(np.isin(i, bad) | np.isin(j, bad))
+    idx = colex(i[ok], j[ok])
+    for f in (lambda X: ps.ps2(X, tile=tile)[0], lambda X: ps.ps2_batched([X], tile=tile)[0][0]):
+        clean, got = host(f(Vd))[idx], host(f(Wd))[idx]
+        assert np.array_equal(got.view(np.uint32), clean.view(np.uint32))
+    i, j, k = np.array([t for t in itertools.combinations(
+        [v for v in range(150) if v not in bad], 3)]).T
+    idx = jslab(150, i, j, k)
+    clean = host(ps.ps3(Vd, tile=tile))[idx]
+    got = host(ps.ps3(Wd, tile=tile))[idx]
+    assert np.array_equal(got.view(np.uint32), clean.view(np.uint32))
