@@ -113,9 +113,10 @@ typedef enum {
                             n_v < 2^21).  Otherwise the
                             planes are written to the workspace first (levels
                             x n_f rounded up to 128 fields per row, one byte
-                            per value for int8, half a byte for FP4) and 256
-                            plane rows must span < 2^31 bytes.  Beyond these
-                            limits: PS_ERR_UNSUPPORTED */
+                            per value for int8; FP4 by name reserves half a
+                            byte) and 256 plane rows of that size must span
+                            < 2^31 bytes.  Beyond these limits:
+                            PS_ERR_UNSUPPORTED */
     PS_PATH_MFMA_FP4 = 3, /* U8 only: the same 0/1 planes, one bit per value in the
                             workspace, expanded in registers to FP4 (e2m1)
                             operands of the matrix cores, FP32 accumulation
@@ -164,7 +165,10 @@ ps_status ps_vector_sums(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
                          hipStream_t stream);
 
 /* Workspace bytes that ps2_compute needs for these arguments (0 if none).
- * s_given / n2 are as they will be passed to ps2_compute. */
+ * s_given / n2 are as they will be passed to ps2_compute.  For path AUTO on
+ * integer levels they include the planes of bits; with less, down to the size
+ * for path VALU, ps2_compute and ps3_compute run the same sums without planes
+ * (slower, same results). */
 size_t ps2_workspace_size(int32_t dtype, int64_t n_f, int64_t n_v,
                           int32_t s_given, const ps_opts* opts);
 

@@ -194,12 +194,27 @@ int choose_path(int32_t dt, const ps_opts* o, int way, int64_t n_f, int64_t n_v,
                                                                       : PS_PATH_VALU;
 }
 
-int path_without_planes(int32_t dt, const ps_opts* o, int64_t n_f, int64_t n_v, int64_t ld) {
+int path_without_planes(int32_t dt, const ps_opts* o, int way, int64_t n_f, int64_t n_v,
+                        int64_t ld) {
     const int levels = o ? o->levels : 0;
-    return dt == PS_U8 && mfma_fused(n_f, levels, 0, 0) &&
-                   mfma_can(PS_PATH_MFMA, 3, n_f, n_v, levels, 0, ld)
+    const int wide = way == 2 && o && o->tile == 2;
+    return dt == PS_U8 && mfma_fused(n_f, levels, 0, wide) &&
+                   mfma_can(PS_PATH_MFMA, way, n_f, n_v, levels, wide, ld)
                ? PS_PATH_MFMA
                : PS_PATH_VALU;
+}
+
+// AUTO reserves the planes of bits themselves.  Path FP4 by name reserves half a
+// byte per value and level, four times as much, which programs may have computed
+// for themselves, and so does a tuned entry that takes it for a triangle below
+// kBpMinVectors.
+size_t plane_bytes(const ps_opts* o, int way, int path, int64_t n_f, int64_t n_v) {
+    const int levels = o ? o->levels : 0;
+    if (path == PS_PATH_MFMA_FP4 && o && o->path == PS_PATH_AUTO &&
+        (way == 3 || n_v >= kBpMinVectors))
+        return bp_bytes(n_f, n_v, levels);
+    return mfma_workspace_bytes(n_f, n_v, levels, path == PS_PATH_MFMA_FP4 ? 1 : 0,
+                                way == 2 && o && o->tile == 2);
 }
 
 int mfma_group(int64_t n_f, int64_t n_v) {

@@ -171,9 +171,19 @@ static hipError_t launch_mgb(int32_t dt, const MgBatchLaunch& a, hipStream_t st)
     }
 }
 
+// Whether a call of path AUTO without room for the planes of bits can run on a path
+// that has none; o: its options.
+static bool without_planes(int path, int32_t dt, const ps_opts* opts, int way, int64_t n_f,
+                           int64_t n_v, int64_t ld, ps_opts* o) {
+    if (path != PS_PATH_MFMA_FP4 || opts->path != PS_PATH_AUTO) return false;
+    *o = *opts;
+    o->path = path_without_planes(dt, opts, way, n_f, n_v, ld);
+    return o->path == PS_PATH_MFMA || 255 * n_f < ((int64_t)1 << 31);
+}
+
 // Sizes of the 2-way workspace regions.  Returns total bytes.
 static size_t ws2_layout(int32_t dt, int64_t n_f, int64_t n_v, int32_t s_given, int path,
-                         int levels, int wide, int32_t nchunks, void* ws, double** s_ws,
+                         const ps_opts* o, int32_t nchunks, void* ws, double** s_ws,
                          int8_t** planes, float** partial) {
     Carver c(ws);
     double* s = nullptr;
@@ -181,8 +191,7 @@ static size_t ws2_layout(int32_t dt, int64_t n_f, int64_t n_v, int32_t s_given, 
     int8_t* pl = nullptr;
     float* part = nullptr;
     if (is_mfma(path) && dt == PS_U8)
-        pl = (int8_t*)c.take(
-            mfma_workspace_bytes(n_f, n_v, levels, path == PS_PATH_MFMA_FP4 ? 1 : 0, wide));
+        pl = (int8_t*)c.take(plane_bytes(o, 2, path, n_f, n_v));
     else if (path == PS_PATH_BITS && dt == PS_U8)   // the packed bits
         pl = (int8_t*)c.take(bits_bytes(n_f, n_v));
     else if (nchunks > 1)
@@ -234,8 +243,8 @@ size_t ps2_workspace_size(int32_t dtype, int64_t n_f, int64_t n_v, int32_t s_giv
                          ? Split{1, 0}
                          : plan_split(dtype, n_f, n_v,
                                       choose_cfg(dtype, 2, PS_PATH_VALU, n_f, n_v, opts), opts);
-    return ws2_layout(dtype, n_f, n_v, s_given, path, opts ? opts->levels : 0,
-                      opts && opts->tile == 2, sp.nchunks, nullptr, nullptr, nullptr, nullptr);
+    return ws2_layout(dtype, n_f, n_v, s_given, path, opts, sp.nchunks, nullptr, nullptr, nullptr,
+                      nullptr);
 }
 
 // ps2_compute over the tiles of one shard (nshards > 1, see
@@ -270,8 +279,12 @@ static ps_status ps2_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
                          : choose_cfg(dtype, 2, PS_PATH_VALU, n_f, n_v, opts);
     // a shard takes the whole call's field-chunk plan: its workspace and sums are the same
     const Split sp = bits ? Split{1, 0} : plan_split(dtype, n_f, n_v, cfg, opts);
-    const size_t need = ws2_layout(dtype, n_f, n_v, s != nullptr, path, levels, wide,
-                                   sp.nchunks, workspace, &s_ws, &planes, &partial);
+    const size_t need = ws2_layout(dtype, n_f, n_v, s != nullptr, path, opts, sp.nchunks,
+                                   workspace, &s_ws, &planes, &partial);
+    ps_opts o;
+    if (ws_bytes < need && without_planes(path, dtype, opts, 2, n_f, n_v, ld, &o))
+        return ps2_run(V, dtype, n_f, n_v, ld, s, c2, n2, shard, nshards, workspace, ws_bytes, &o,
+                       stream);
     if (ws_bytes < need || (need && !workspace))
         return fail(PS_ERR_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, need);
     if (!aligned(workspace, 256)) return fail(PS_ERR_ARG, "workspace is not 256-byte aligned");
@@ -452,9 +465,8 @@ size_t ps3_workspace_size(int32_t dtype, int64_t n_f, int64_t n_v, int32_t s_giv
     const int path = choose_path(dtype, opts, 3, n_f, n_v, n_f);
     if (is_mfma(path) && dtype == PS_U8)
         return ws3_layout(n_v, npre, s_given, n2_given, 4, 1, 1, stage,
-                          mfma_workspace_bytes(n_f, n_v, opts ? opts->levels : 0,
-                                               path == PS_PATH_MFMA_FP4 ? 1 : 0, 0),
-                          nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+                          plane_bytes(opts, 3, path, n_f, n_v), nullptr, nullptr, nullptr,
+                          nullptr, nullptr, nullptr);
     const Split sp2 =
         plan_split(dtype, n_f, n_v, choose_cfg(dtype, 2, PS_PATH_VALU, n_f, n_v, opts), opts);
     return ws3_layout(n_v, npre, s_given, n2_given, dtype == PS_F64 ? 8 : 4, sp2.nchunks,
@@ -568,23 +580,21 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
     if (!c3) return fail(PS_ERR_ARG, "c3 is NULL");
     if (!aligned(c3, 4) || !aligned(n2, 4) || !aligned(s, 8))
         return fail(PS_ERR_ARG, "misaligned output, n2 or sums pointer");
-    if (from_scratch) {
+    ps_opts o;
+    const bool way_back = without_planes(path, dtype, opts, 3, n_f, n_v, ld, &o);
+    if (from_scratch || way_back) {
         const size_t need = ps3_workspace_size(dtype, n_f, n_v, s != nullptr, n2 != nullptr,
                                                j_begin, j_end, opts);
-        // AUTO's planes may not fit where the int8 path, which has none, does
-        if (need > ws_bytes && path == PS_PATH_MFMA_FP4 && opts->path == PS_PATH_AUTO) {
-            ps_opts o = *opts;
-            o.path = path_without_planes(dtype, opts, n_f, n_v, ld);
+        if (need > ws_bytes && way_back)
             return ps3_run(V, dtype, n_f, n_v, ld, s, n2, j_begin, j_end, c3, workspace, ws_bytes,
-                           true, &o, stream);
-        }
-        if (need > ws_bytes)
+                           from_scratch, &o, stream);
+        if (need > ws_bytes && from_scratch)
             return fail(PS_ERR_WORKSPACE,
                         "ps3_compute_noalloc: this call needs %zu bytes of scratch, the static "
                         "scratch holds %zu (pass s and n2, use a shorter j range, or call "
                         "ps3_compute with a workspace)", need, ws_bytes);
-        if ((st = scratch_of_current_device(&workspace)) != PS_OK) return st;
     }
+    if (from_scratch && (st = scratch_of_current_device(&workspace)) != PS_OK) return st;
     double* s_ws = nullptr;
     void* n2_ws = nullptr;
     int64_t* prefix = nullptr;
@@ -594,11 +604,11 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
     // tile configuration (those are the VALU tiles)
     if ((path == PS_PATH_MFMA_FP4 || (bits && opts->tile == 0)) && bp3_fits(n_f, n_v, levels))
         return ps3_bp(V, n_f, n_v, ld, s, n2, j_begin, j_end, c3, workspace, ws_bytes, levels,
-                      bits ? bits_bytes(n_f, n_v) : mfma_workspace_bytes(n_f, n_v, levels, 1, 0),
-                      stream);
+                      bits ? bits_bytes(n_f, n_v) : plane_bytes(opts, 3, path, n_f, n_v), stream);
     // stages of more vectors than the planes' 32-bit offsets allow: the same sums on
     // another path (its workspace is no larger)
-    const int run = path == PS_PATH_MFMA_FP4 ? path_without_planes(dtype, opts, n_f, n_v, ld) : path;
+    const int run =
+        path == PS_PATH_MFMA_FP4 ? path_without_planes(dtype, opts, 3, n_f, n_v, ld) : path;
     if (run == PS_PATH_MFMA)
         return ps3_mfma(V, n_f, n_v, ld, s, n2, j_begin, j_end, c3, workspace, ws_bytes, levels,
                         path == run ? opts->tile : 0, stream);

@@ -290,9 +290,13 @@ bool is_mfma(int path);
 // (mfma_ld_fits on the fused path, mfma_row_fits on planes); else VALU.  ld
 // is the row stride (n_f in size queries).
 int choose_path(int32_t dt, const ps_opts* o, int way, int64_t n_f, int64_t n_v, int64_t ld);
-// The 3-way path AUTO takes for levels 1..15 where the FP4 path's planes have no room:
-// int8 MFMA when it can take the shape, else VALU.
-int path_without_planes(int32_t dt, const ps_opts* o, int64_t n_f, int64_t n_v, int64_t ld);
+// The path AUTO takes for levels 1..15 where the FP4 path's planes have no room:
+// int8 MFMA with its planes formed in registers when it can take the shape, else VALU.
+int path_without_planes(int32_t dt, const ps_opts* o, int way, int64_t n_f, int64_t n_v,
+                        int64_t ld);
+// Workspace bytes of a uint8 call's planes on a matrix-core path (0 where they are
+// formed in registers).
+size_t plane_bytes(const ps_opts* o, int way, int path, int64_t n_f, int64_t n_v);
 // Tile order of the fused 2-way int8 MFMA kernel: block columns are walked in
 // groups of mfma_group(...) columns (a tuned entry for path MFMA registers
 // idx, the group being 2^idx; default 4).
@@ -536,6 +540,9 @@ struct BpLaunch {
     float* c3;
 };
 int64_t bp_row_words(int64_t n_f, int levels);
+inline size_t bp_bytes(int64_t n_f, int64_t n_v, int levels) {
+    return (size_t)n_v * (size_t)bp_row_words(n_f, levels) * sizeof(uint32_t);
+}
 // Whether the bit planes hold the shape: sums exact in FP32, and for the 3-way
 // slices all planes and the whole pair table within 32-bit byte offsets.
 inline bool bp_exact(int64_t n_f, int levels) {

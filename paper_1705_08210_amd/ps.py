@@ -152,6 +152,18 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
 
 
+def _room(query, dt: int, o: Opts, device) -> torch.Tensor:
+    """The workspace of a call, query(opts) bytes.  Where the device has no room for
+    the planes of bits that path AUTO takes for integer levels, the workspace of
+    the paths without them, which the call then runs on."""
+    try:
+        return _workspace(query(o), device)
+    except torch.OutOfMemoryError:
+        if dt != PS_U8 or o.path != PATH["auto"]:
+            raise
+        return _workspace(query(Opts(o.acc, PATH["valu"], o.levels, o.tile)), device)
+
+
 def n2_dtype(V_dtype) -> torch.dtype:
     if V_dtype == torch.uint8:
         return torch.int32
@@ -184,8 +196,8 @@ def ps2(V: torch.Tensor, s: torch.Tensor | None = None, want_c2: bool = True,
         if want_n2 and n2 is None:
             n2 = torch.empty(m, dtype=n2_dtype(V.dtype), device=V.device)
         o = _opts(acc, path, levels, tile)
-        ws_n = lib.ps2_workspace_size(dt, n_f, n_v, int(s is not None), ctypes.byref(o))
-        ws = _workspace(ws_n, V.device)
+        ws = _room(lambda q: lib.ps2_workspace_size(dt, n_f, n_v, int(s is not None),
+                                                    ctypes.byref(q)), dt, o, V.device)
         _check(lib.ps2_compute(V.data_ptr(), dt, n_f, n_v, ld, _ptr(s), _ptr(c2), _ptr(n2),
                                ws.data_ptr(), ws.numel(), ctypes.byref(o), _stream(stream)))
     return c2, n2
@@ -234,9 +246,9 @@ def ps3(V: torch.Tensor, s: torch.Tensor | None = None, n2: torch.Tensor | None 
         if c3 is None:
             c3 = torch.empty(m, dtype=torch.float32, device=V.device)
         o = _opts(acc, path, levels, tile)
-        ws_n = lib.ps3_workspace_size(dt, n_f, n_v, int(s is not None), int(n2 is not None),
-                                      j_begin, j_end, ctypes.byref(o))
-        ws = _workspace(ws_n, V.device)
+        ws = _room(lambda q: lib.ps3_workspace_size(dt, n_f, n_v, int(s is not None),
+                                                    int(n2 is not None), j_begin, j_end,
+                                                    ctypes.byref(q)), dt, o, V.device)
         _check(lib.ps3_compute(V.data_ptr(), dt, n_f, n_v, ld, _ptr(s), _ptr(n2), j_begin,
                                j_end, c3.data_ptr() if m > 0 else None, ws.data_ptr(),
                                ws.numel(), ctypes.byref(o), _stream(stream)))
@@ -364,9 +376,9 @@ class Plan3:
         self.V, self.s, self.n2 = V, s, n2
         self.c3 = c3 if c3 is not None else torch.empty(m, dtype=torch.float32, device=V.device)
         o = _opts(acc, path, levels, tile)
-        ws_n = lib.ps3_workspace_size(dt, n_f, n_v, int(s is not None), int(n2 is not None),
-                                      j_begin, j_end, ctypes.byref(o))
-        self.ws = _workspace(ws_n, V.device)
+        self.ws = _room(lambda q: lib.ps3_workspace_size(dt, n_f, n_v, int(s is not None),
+                                                         int(n2 is not None), j_begin, j_end,
+                                                         ctypes.byref(q)), dt, o, V.device)
         self._home = torch.cuda.current_stream(V.device)
         h = P()
         _check(lib.ps_plan_create_3way(ctypes.byref(h), V.data_ptr(), dt, n_f, n_v, ld, _ptr(s),
