@@ -72,12 +72,29 @@ int small2(int32_t dt, int64_t n_f, int64_t n_v, int cfg, int32_t nchunks, const
     return tri_tiles(n_v, 32) * nchunks <= 320 ? 8 : 4;
 }
 
-// As small2 for the slices (the rule looks at the vectors alone, so that a
-// stage sums as the whole run does).  FP32, us, 64 x 64 tiles and finish / 32 x
-// 32: 385 fields, 64 vectors 79 / 25, 150 85 / 44, 200 95 / 61, 255 134 / 121;
-// 8000 fields, 64 vectors 474 / 132, 200 850 / 820, 255 1389 / 2089.
-int small3(int64_t n_v, const ps_opts* o) {
+// As small2 for the slices.  The rule looks at the whole run (n_v vectors, nchunks
+// field chunks), never at the stage, so that a stage sums as the whole run does.
+// Unsplit sums take the small tiles up to 208 vectors at any number of fields: the
+// 64 x 64 tiles are too few there.  Whole calls, us, 64 x 64 / 32 x 32:
+//   FP32 385 fields, 64 vectors 79 / 25, 150 85 / 44, 200 95 / 61, 255 134 / 121;
+//   4096 fields, 208 vectors 601 / 499
+//   FP64 4000 fields, 208 vectors 903 / 819; uint8 40000 fields, 208 vectors 1848 / 995
+// Field chunks bring the 64 x 64 tiles more workgroups, and past the work at which
+// they fill the chip the doubled operand traffic of the small ones loses:
+//   FP32 (two, three chunks) 6000 fields, 208 vectors 608 / 562; 8192, 180 727 / 706,
+//   190 725 / 779; 12000, 130 622 / 530, 160 745 / 692, 170 852 / 871, 208 1139 / 1302
+//   FP32 (more) 20000 fields, 110 vectors 660 / 615, 120 653 / 725; 40000 fields, 80
+//   737 / 496, 130 1152 / 1583, 208 2967 / 4064
+//   FP16 12000 fields, 160 vectors 437 / 406, 208 716 / 742; 40000, 120 595 / 744
+// One stage of few slabs is still faster in small tiles beyond the line (12000
+// fields, 208 vectors, one slab 548 / 152), at the price of other sums than the run's.
+// Eight waves up to 96 vectors, where the tiles leave CUs idle (four / eight waves,
+// FP32: 385 fields, 48 vectors 28 / 23, 96 28 / 25, 100 30 / 30, 128 35 / 39; 4000
+// fields, 96 vectors 144 / 103, 100 155 / 163, 150 295 / 254, 180 376 / 364).
+int small3(int64_t n_f, int64_t n_v, int32_t nchunks, const ps_opts* o) {
     if ((o && o->tile > 0) || n_v > 208) return 0;
+    const int64_t limit = nchunks > 3 ? 30000000000 : 55000000000;
+    if (nchunks > 1 && n_v * n_v * n_v > limit / n_f) return 0;
     return n_v <= 96 ? 8 : 4;
 }
 

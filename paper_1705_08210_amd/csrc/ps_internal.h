@@ -276,7 +276,7 @@ int choose_cfg(int32_t dt, int32_t way, int32_t path, int64_t n_f, int64_t n_v,
 // 3-way launch, runs the 32 x 32 tiles of mgemm_small.h (o->tile = 0 only);
 // 0 if not.
 int small2(int32_t dt, int64_t n_f, int64_t n_v, int cfg, int32_t nchunks, const ps_opts* o);
-int small3(int64_t n_v, const ps_opts* o);
+int small3(int64_t n_f, int64_t n_v, int32_t nchunks, const ps_opts* o);
 int choose_acc(int64_t n_f, const ps_opts* o);
 int32_t split_chunks(int32_t dt, int64_t n_f, int acc);
 int64_t chunk_tiles(int32_t dt, int cfg);

@@ -95,3 +95,24 @@ def test_3way(kind, n_v, n_f):
     parts = [host(ps.ps3(Vd, s=s, n2=n2, j_begin=a, j_end=b)) for a, b in zip(cuts, cuts[1:])]
     assert sum(p.size for p in parts) == int(slab_off(n_v, n_v - 1))
     assert np.array_equal(np.concatenate(parts).view(np.uint32), full.view(np.uint32))
+
+
+@pytest.mark.parametrize("kind", ["f32", "f16"])
+@pytest.mark.parametrize("n_v,n_f", [(120, 17361), (120, 17362), (208, 6111), (208, 6112)])
+def test_3way_rule_edges_of_split_sums(kind, n_v, n_f):
+    """The last field counts of the small tiles (more than three field chunks, and
+    up to three) and the first of the 64 x 64 ones; stages keep the run's bits."""
+    import librules
+    from paper_1705_08210_amd import ps
+    small = librules.small3(n_f, n_v, -(-n_f // 4096)) > 0
+    assert small == (n_f in (17361, 6111))
+    V = _data(kind, n_v, n_f, seed=n_f)
+    announce(f"small 3-way rule {kind} {n_v}x{n_f}")
+    Vd = to_dev(V)
+    full = host(ps.ps3(Vd))
+    _check(full, oracle.c3_all(V), kind, "c3")
+    s, _ = ps.vector_sums(Vd)
+    _, n2 = ps.ps2(Vd, s=s, want_c2=False, want_n2=True)
+    cuts = [1, 2, n_v // 2, n_v - 1]
+    parts = [host(ps.ps3(Vd, s=s, n2=n2, j_begin=a, j_end=b)) for a, b in zip(cuts, cuts[1:])]
+    assert np.array_equal(np.concatenate(parts).view(np.uint32), full.view(np.uint32))
