@@ -658,7 +658,7 @@ static ps_status ps3_run(const void* V, int32_t dtype, int64_t n_f, int64_t n_v,
     // one launch over the split tiling of the stage: colex (pair, k) tiles of
     // the slabs below js, lex (pair, i) tiles of the others
     const int64_t js = split3(n_v, j_begin, j_end);
-    const int small = small3(n_f, n_v, nchunks, opts);
+    const int small = bits ? 0 : small3(n_f, n_v, nchunks, opts);
     const int64_t nt0 = small ? 0 : flat_tiles(n_v, j_begin, js, bm);
     Mg3Launch a{KV, kn_f, n_v, kld, s, n2, j_begin, j_end, c3, prefix,
                 small ? 0 : nt0 + lex_tiles(n_v, js, j_end, bm), cfg, nchunks,

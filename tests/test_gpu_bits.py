@@ -111,3 +111,21 @@ def test_bits_3way_sampled():
     c3 = host(ps.ps3(to_dev(V), path="bits", levels=1))
     i, j, k = sample_triples(900, 4096, seed=46)
     check_exact_f32(c3[jslab(900, i, j, k)], oracle.c3_triples(V, i, j, k), "c3 sampled")
+
+
+@pytest.mark.parametrize("n_v,n_f", [(5, (1 << 24) - 1), (5, 1 << 24), (7, (1 << 24) + 100)])
+def test_fields_around_the_exact_range_of_the_planes(n_v, n_f):
+    """The last field count of the planes of bits, and rows past it, which run the
+    popcount tiles: 2-way, 3-way and a stage of it."""
+    from paper_1705_08210_amd import ps
+    V = (np.random.default_rng(n_f).random((n_v, n_f), dtype=np.float32) < 0.3).astype(np.uint8)
+    announce(f"bits {n_v}x{n_f}")
+    Vd = to_dev(V)
+    c2, n2 = ps.ps2(Vd, want_n2=True, path="bits", levels=1)
+    ref, rn2 = oracle.c2_all(V, with_n2=True)
+    check_exact_f32(host(c2), ref, "c2")
+    assert np.array_equal(host(n2).astype(np.float64), rn2)
+    full = host(ps.ps3(Vd, path="bits", levels=1))
+    check_exact_f32(full, oracle.c3_all(V), "c3")
+    part = host(ps.ps3(Vd, n2=n2, j_begin=2, j_end=n_v - 1, path="bits", levels=1))
+    assert np.array_equal(part.view(np.uint32), full[ps.stage_size(n_v, 1, 2):].view(np.uint32))
