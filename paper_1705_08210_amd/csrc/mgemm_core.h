@@ -198,11 +198,9 @@ struct Stager {
 
     // rows [row0, row0 + BM) of V, valid below row_end; field-tile byte
     // offset kb0; nbytes = n_f * element size; ldb = row pitch in bytes.
-    // XJ: replace each word by min(word, word of row xrow) (X_j staging).
-    template <int DT, bool XJ, bool VEC>
+    template <int DT, bool VEC>
     __device__ __forceinline__ void load(const char* Vb, int64_t ldb, int64_t row0,
-                                         int64_t row_end, int64_t kb0, int64_t nbytes,
-                                         const char* xrow) {
+                                         int64_t row_end, int64_t kb0, int64_t nbytes) {
         constexpr int ESZ = Ops<DT>::kEsz;
 #pragma unroll
         for (int c = 0; c < kCh; ++c) {
@@ -213,15 +211,14 @@ struct Stager {
             const int64_t b0 = kb0 + ch * 16;
             uint4 v = make_uint4(0, 0, 0, 0);
             if (grow < row_end) v = load_chunk<ESZ, VEC>(Vb + grow * ldb, b0, nbytes);
-            if (XJ) v = xmin_chunk<DT>(v, load_chunk<ESZ, VEC>(xrow, b0, nbytes));
             r[c] = v;
         }
     }
 
     // Rows given per chunk (the flattened 3-way rows): roff[c] is the byte
-    // offset of chunk c's row (< 0: no row, zero fill) and, with XJ, xoff[c]
-    // the offset of the row v_j it is min-ed with.
-    template <int DT, bool XJ, bool VEC>
+    // offset of chunk c's row (< 0: no row, zero fill) and xoff[c] the offset of
+    // the row it is min-ed with.
+    template <int DT, bool VEC>
     __device__ __forceinline__ void load_rows(const char* Vb, const int64_t (&roff)[kCh],
                                               const int64_t (&xoff)[kCh], int64_t kb0,
                                               int64_t nbytes) {
@@ -233,7 +230,7 @@ struct Stager {
             uint4 v = make_uint4(0, 0, 0, 0);
             if (roff[c] >= 0) {
                 v = load_chunk<ESZ, VEC>(Vb + roff[c], b0, nbytes);
-                if (XJ) v = xmin_chunk<DT>(v, load_chunk<ESZ, VEC>(Vb + xoff[c], b0, nbytes));
+                v = xmin_chunk<DT>(v, load_chunk<ESZ, VEC>(Vb + xoff[c], b0, nbytes));
             }
             r[c] = v;
         }
@@ -316,15 +313,15 @@ using MicroAcc = typename Ops<DT>::Acc[Micro<DT, TM>::kR][Micro<DT, TM>::kC];
 
 // ---------------------------------------------------------------------------
 // One output tile.  acc receives the sums for the lane's micro-tile.
-//   A rows [a_row0, a_row0 + BM) valid below a_end (optionally X_j-staged
-//   against row xj), B rows [b_row0, b_row0 + BN) valid below b_end.
+//   A rows [a_row0, a_row0 + BM) valid below a_end, B rows [b_row0, b_row0 + BN)
+//   valid below b_end.
 //   active: whether this wave does the arithmetic.
 //   [kt0, kt1): the field tiles summed (kt1 < 0: all of them).
 // ---------------------------------------------------------------------------
-template <int DT, int TM, int TN, int BKW, bool XJ, bool VEC>
+template <int DT, int TM, int TN, int BKW, bool VEC>
 __device__ __forceinline__ void run_tile_body(const char* Vb, int64_t ldb, int64_t nbytes,
                                               int64_t a_row0, int64_t a_end, int64_t b_row0,
-                                              int64_t b_end, const char* xrow, bool active,
+                                              int64_t b_end, bool active,
                                               typename Ops<DT>::Word* As,
                                               typename Ops<DT>::Word* Bs,
                                               typename Ops<DT>::Acc (&acc)[TM][TN],
@@ -349,32 +346,23 @@ __device__ __forceinline__ void run_tile_body(const char* Vb, int64_t ldb, int64
     const int64_t tile_bytes = (int64_t)BKW * (int64_t)sizeof(Word);
     const int64_t nk_all = (nbytes + tile_bytes - 1) / tile_bytes;
     const int64_t nk = kt1 < 0 || kt1 > nk_all ? nk_all : kt1;
-    // 2-way tiles prefetch the next field tile into registers while
-    // computing; the 3-way slices (which also stage v_j) load each tile just
-    // before staging it and rely on the other resident workgroups to cover
-    // the latency.
-    constexpr bool kPrefetch = !XJ;
+    // 2-way tiles prefetch the next field tile into registers while computing
     SA sa;
     SB sb;
-    if (kPrefetch && kt0 < nk) {
+    if (kt0 < nk) {
         const int64_t kb = kt0 * tile_bytes;
-        sa.template load<DT, XJ, VEC>(Vb, ldb, a_row0, a_end, kb, nbytes, xrow);
-        sb.template load<DT, false, VEC>(Vb, ldb, b_row0, b_end, kb, nbytes, nullptr);
+        sa.template load<DT, VEC>(Vb, ldb, a_row0, a_end, kb, nbytes);
+        sb.template load<DT, VEC>(Vb, ldb, b_row0, b_end, kb, nbytes);
     }
     for (int64_t kt = kt0; kt < nk; ++kt) {
-        if (!kPrefetch) {
-            const int64_t kb = kt * tile_bytes;
-            sa.template load<DT, XJ, VEC>(Vb, ldb, a_row0, a_end, kb, nbytes, xrow);
-            sb.template load<DT, false, VEC>(Vb, ldb, b_row0, b_end, kb, nbytes, nullptr);
-        }
         __syncthreads();  // previous tile's LDS reads are done
         sa.store(As);
         sb.store(Bs);
         __syncthreads();
-        if (kPrefetch && kt + 1 < nk) {  // prefetch the next field tile into registers
+        if (kt + 1 < nk) {
             const int64_t kb = (kt + 1) * tile_bytes;
-            sa.template load<DT, XJ, VEC>(Vb, ldb, a_row0, a_end, kb, nbytes, xrow);
-            sb.template load<DT, false, VEC>(Vb, ldb, b_row0, b_end, kb, nbytes, nullptr);
+            sa.template load<DT, VEC>(Vb, ldb, a_row0, a_end, kb, nbytes);
+            sb.template load<DT, VEC>(Vb, ldb, b_row0, b_end, kb, nbytes);
         }
         if (!active) continue;
         constexpr int kUnroll = DT == PS_U8 ? PS_UNROLL_PLAIN / 2 : PS_UNROLL_PLAIN;
@@ -453,12 +441,11 @@ __device__ __forceinline__ void run_tile(const char* Vb, int64_t ldb, int64_t nb
         else
             run_half<TM, BKW, false, false>(Vb, nbytes, ra, ra, rb, active, As, Bs, acc, kt0, kt1);
     } else if (vec) {
-        run_tile_body<DT, TM, TM, BKW, false, true>(Vb, ldb, nbytes, a_row0, a_end, b_row0, b_end,
-                                                    nullptr, active, As, Bs, acc, kt0, kt1);
+        run_tile_body<DT, TM, TM, BKW, true>(Vb, ldb, nbytes, a_row0, a_end, b_row0, b_end, active,
+                                             As, Bs, acc, kt0, kt1);
     } else {
-        run_tile_body<DT, TM, TM, BKW, false, false>(Vb, ldb, nbytes, a_row0, a_end, b_row0,
-                                                     b_end, nullptr, active, As, Bs, acc, kt0,
-                                                     kt1);
+        run_tile_body<DT, TM, TM, BKW, false>(Vb, ldb, nbytes, a_row0, a_end, b_row0, b_end, active,
+                                              As, Bs, acc, kt0, kt1);
     }
 }
 
@@ -496,29 +483,26 @@ __device__ __forceinline__ void run_tile_flat_body(
     const int64_t nk_all = (nbytes + tile_bytes - 1) / tile_bytes;
     const int64_t nk = kt1 < 0 || kt1 > nk_all ? nk_all : kt1;
     // The plain B rows of the next field tile are prefetched into registers
-    // while this one is consumed, for the FP32 / FP16 tiles that stage two
+    // while this one is consumed, for the FP32 tiles that stage two
     // B chunks per thread (measured on sparse_4096x1024, FP32: 128 x 128
     // tiles with 16-word field tiles 26.5 -> 25.5 ms, 64 x 64 28.7 -> 28.3
     // ms; the 128 x 128 tiles with 32-word field tiles stage four, lose a
     // wave per SIMD to the extra registers and ran 28.1 -> 33.5 ms).
-    constexpr bool kPrefetchB = (DT == PS_F32 || DT == PS_F16) && SB::kCh <= 2;
+    constexpr bool kPrefetchB = DT == PS_F32 && SB::kCh <= 2;
     SA sa;
     SB sb;
     if (kPrefetchB && kt0 < nk)
-        sb.template load<DT, false, VEC>(Vb, ldb, b_row0, b_end, kt0 * tile_bytes, nbytes,
-                                         nullptr);
+        sb.template load<DT, VEC>(Vb, ldb, b_row0, b_end, kt0 * tile_bytes, nbytes);
     for (int64_t kt = kt0; kt < nk; ++kt) {
         const int64_t kb = kt * tile_bytes;
-        sa.template load_rows<DT, true, VEC>(Vb, aoff, xoff, kb, nbytes);
-        if (!kPrefetchB)
-            sb.template load<DT, false, VEC>(Vb, ldb, b_row0, b_end, kb, nbytes, nullptr);
+        sa.template load_rows<DT, VEC>(Vb, aoff, xoff, kb, nbytes);
+        if (!kPrefetchB) sb.template load<DT, VEC>(Vb, ldb, b_row0, b_end, kb, nbytes);
         __syncthreads();  // previous tile's LDS reads are done
         sa.store(As);
         sb.store(Bs);
         __syncthreads();
         if (kPrefetchB && kt + 1 < nk)
-            sb.template load<DT, false, VEC>(Vb, ldb, b_row0, b_end, kb + tile_bytes, nbytes,
-                                             nullptr);
+            sb.template load<DT, VEC>(Vb, ldb, b_row0, b_end, kb + tile_bytes, nbytes);
         if (!active) continue;
         constexpr int kUnroll = DT == PS_U8 ? PS_UNROLL_PLAIN / 2 : PS_UNROLL_PLAIN;
 #pragma unroll kUnroll

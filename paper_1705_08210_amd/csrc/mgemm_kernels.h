@@ -386,7 +386,8 @@ __global__ __launch_bounds__(kThreads, (min_waves<DT, TM, BKW>())) void ps_mgb_k
 
 template <int DT, int TM, int BKW>
 hipError_t go_mg2(const Mg2Call& a, hipStream_t st) {
-    if (a.small) return go_sm2<DT>(a, st);
+    if constexpr (DT != PS_B1)   // packed bits never take the small tiles
+        if (a.small) return go_sm2<DT>(a, st);
     const int64_t T = shard_tiles(tri_tiles(a.n_v, 16 * TM), a.shard0, a.nshards);
     if (T == 0) return hipSuccess;
     return launch_items(chunk_items(T, a.nchunks), kThreads, kXcds, [&](unsigned grid, int64_t item0) {
@@ -409,7 +410,8 @@ hipError_t go_mg3(const Mg3Launch& a, hipStream_t st) {
 // configuration cfg.
 template <int DT, class Dispatch>
 hipError_t go_mg3_all(const Mg3Launch& a, Dispatch dispatch, hipStream_t st) {
-    if (slab_small(a.mode)) return go_sm3<DT>(a, st);
+    if constexpr (DT != PS_B1)
+        if (slab_small(a.mode)) return go_sm3<DT>(a, st);
     return dispatch(a.cfg, [&](auto tm, auto bkw) {
         return go_mg3<DT, decltype(tm)::value, decltype(bkw)::value>(a, st);
     });

@@ -189,13 +189,11 @@ __global__ __launch_bounds__(64 * NW, 2) void ps_sm2_kernel(Mg2Call a, int64_t n
     const char* V = (const char*)a.V;
     const int64_t w = item0 + blockIdx.x, nitems = ntiles * a.nchunks;
     if (w >= nitems) {
-        if constexpr (DT != PS_B1) {
-            const int64_t i = (w - nitems) * NW + threadIdx.x / 64;
-            if (a.s_out && i < a.n_v) {
-                int bad;
-                const double x = wave_row_sum<DT>(V + i * ldb, a.n_f, VEC, bad);
-                if (threadIdx.x % 64 == 0) a.s_out[i] = x;
-            }
+        const int64_t i = (w - nitems) * NW + threadIdx.x / 64;
+        if (a.s_out && i < a.n_v) {
+            int bad;
+            const double x = wave_row_sum<DT>(V + i * ldb, a.n_f, VEC, bad);
+            if (threadIdx.x % 64 == 0) a.s_out[i] = x;
         }
         return;
     }
@@ -238,7 +236,7 @@ template <int DT>
 __device__ __forceinline__ void sm3_store(const Mg3Launch& a, typename Ops<DT>::Acc acc,
                                           int64_t i, int64_t j, int64_t k, PairT<DT> nxy,
                                           double sz, int64_t idx, int64_t chunk, int64_t stage) {
-    if (DT != PS_F64 && DT != PS_U8 && DT != PS_B1 && a.nchunks > 1) {
+    if (DT != PS_F64 && DT != PS_U8 && a.nchunks > 1) {
         a.partial[chunk * stage + idx] = (float)acc;   // FP32 chunk sums, finished later
         return;
     }
@@ -339,11 +337,6 @@ __global__ __launch_bounds__(64 * NW, 2) void ps_sm3_kernel(Mg3Launch a, Sm3Grid
                 sm3_store<DT>(a, out[f], i0 + f, j, k, njk, DT == PS_U8 ? a.s[i0 + f] : 0.0,
                               base + i0 + f, chunk, stage);
     }
-}
-
-template <int DT>
-bool sm_vec(const void* V, int64_t ld) {
-    return (uintptr_t)V % 16 == 0 && ld * Ops<DT>::kEsz % 16 == 0;
 }
 
 // waves: of a workgroup, 4 or 8.
