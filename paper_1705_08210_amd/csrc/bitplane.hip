@@ -586,6 +586,17 @@ static LvArgs bp_args(const BpLaunch& b) {
     return a;
 }
 
+// The widest shape that still leaves about a workgroup per half CU: 64 x 64
+// tiles, 128 x 128 once there are 128 of them, 256 x 128 once there are
+// 1024 (whole calls, us, three levels of 8000 fields; 256 x 128 / 128 x 128
+// / 64 x 64): 1536 vectors 88 / 57 / 45, 2048 89 / 58 / 64, 4096 136 / 118 /
+// 142, 6000 199 / 186 / 271, 8192 315 / 316 / 482; 400 to 20000 fields and
+// one level cross at the same sizes.
+int bp2_rows(int64_t n_v) {
+    if (tri_tiles(n_v, 256) * 2 >= 1024) return 256;
+    return tri_tiles(n_v, 128) >= 128 ? 128 : 64;
+}
+
 hipError_t launch_bp2(const BpLaunch& b, hipStream_t st) {
     if (b.n_v < 2) return hipSuccess;
     LvArgs a = bp_args(b);
@@ -602,20 +613,17 @@ hipError_t launch_bp2(const BpLaunch& b, hipStream_t st) {
         });
     };
     using std::integral_constant;
-    // The widest shape that still leaves about a workgroup per half CU: 64 x 64
-    // tiles, 128 x 128 once there are 128 of them, 256 x 128 once there are
-    // 1024 (whole calls, us, three levels of 8000 fields; 256 x 128 / 128 x 128
-    // / 64 x 64): 1536 vectors 88 / 57 / 45, 2048 89 / 58 / 64, 4096 136 / 118 /
-    // 142, 6000 199 / 186 / 271, 8192 315 / 316 / 482; 400 to 20000 fields and
-    // one level cross at the same sizes.
-    if (tri_tiles(b.n_v, 256) * 2 >= 1024)
+    switch (bp2_rows(b.n_v)) {
+    case 256:
         return go(integral_constant<int, 4>{}, integral_constant<int, 2>{},
                   integral_constant<int, 3>{});
-    if (tri_tiles(b.n_v, 128) >= 128)
+    case 128:
         return go(integral_constant<int, 2>{}, integral_constant<int, 2>{},
                   integral_constant<int, 4>{});
-    return go(integral_constant<int, 1>{}, integral_constant<int, 1>{},
-              integral_constant<int, 8>{});
+    default:
+        return go(integral_constant<int, 1>{}, integral_constant<int, 1>{},
+                  integral_constant<int, 8>{});
+    }
 }
 
 hipError_t launch_bp3(const BpLaunch& b, hipStream_t st) {

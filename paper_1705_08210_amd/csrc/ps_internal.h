@@ -554,6 +554,7 @@ inline bool bp3_fits(int64_t n_f, int64_t n_v, int levels) {
 // V -> planes; with s, also the per-vector sums.
 hipError_t launch_bp_pack(const uint8_t* V, int64_t n_f, int64_t n_v, int64_t ld, int levels,
                           uint32_t* planes, double* s, hipStream_t st);
+int bp2_rows(int64_t n_v);   // rows of launch_bp2's tiles: 64, 128 or 256
 hipError_t launch_bp2(const BpLaunch& b, hipStream_t st);
 hipError_t launch_bp3(const BpLaunch& b, hipStream_t st);
 // Output reduction (reduce.hip).

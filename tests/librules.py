@@ -14,6 +14,9 @@ def _rule(name, res, *args):
     return f
 
 
+# int bp2_rows(int64_t n_v): rows of the tiles of planes of bits
+bp2_rows = _rule("_ZN2ps8bp2_rowsEl", I32, I64)
+
 # int small3(int64_t n_f, int64_t n_v, int32_t nchunks, const ps_opts*)
 _small3 = _rule("_ZN2ps6small3ElliPK7ps_opts", I32, I64, I64, I32, P)
 
@@ -21,3 +24,14 @@ _small3 = _rule("_ZN2ps6small3ElliPK7ps_opts", I32, I64, I64, I32, P)
 def small3(n_f, n_v, nchunks, tile=0):
     """Waves of the 3-way 32 x 32 tiles, 0: the 64 x 64 tiles."""
     return _small3(n_f, n_v, nchunks, ctypes.byref(ps._opts(tile=tile)))
+
+
+def line(rule, lo, hi):
+    """The first n in (lo, hi] at which rule(n) differs from rule(lo); a rule with
+    one line in the range."""
+    first = rule(lo)
+    assert rule(hi) != first
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if rule(mid) == first else (lo, mid)
+    return hi

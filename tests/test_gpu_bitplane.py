@@ -137,3 +137,26 @@ def test_noalloc_auto_without_room_for_planes():
     ps.ps3_noalloc(V, c3, s=s, n2=n2, j_begin=100, j_end=102, levels=3)
     ref = ps.ps3(V, s=s, n2=n2, j_begin=100, j_end=102, path="mfma", levels=3)
     assert bool((c3 == ref).all())
+
+
+def _shape_sizes():
+    """The last and first sizes of every tile shape, and for the widest one a last
+    row block of one row, of half a block, of one row more, and all but one row."""
+    import librules
+    a = librules.line(librules.bp2_rows, 64, 4096)
+    b = librules.line(librules.bp2_rows, a, 16384)
+    assert [librules.bp2_rows(n) for n in (a - 1, a, b - 1, b)] == [64, 128, 128, 256]
+    c = -(-b // 256) * 256
+    return [a - 1, a, b - 1, b, c + 1, c + 128, c + 129, c + 255]
+
+
+@pytest.mark.parametrize("k", range(8))
+def test_2way_shape_edges(k):
+    from paper_1705_08210_amd import ps
+    n_v = _shape_sizes()[k]
+    for L, kw in ((3, dict(path="mfma_fp4", levels=3)), (1, dict(path="bits", levels=1))):
+        V = to_dev(_levels(n_v, 150, L, seed=n_v))
+        announce(f"bit planes 2-way shape edge n_v={n_v} {kw}")
+        a, na = ps.ps2(V, want_n2=True, **kw)
+        b, nb = ps.ps2(V, want_n2=True, path="valu")
+        assert bool((a == b).all()) and bool((na == nb).all())
