@@ -116,3 +116,49 @@ def test_3way_rule_edges_of_split_sums(kind, n_v, n_f):
     cuts = [1, 2, n_v // 2, n_v - 1]
     parts = [host(ps.ps3(Vd, s=s, n2=n2, j_begin=a, j_end=b)) for a, b in zip(cuts, cuts[1:])]
     assert np.array_equal(np.concatenate(parts).view(np.uint32), full.view(np.uint32))
+
+
+RULE_N_F = {"f32": 1001, "f16": 1001, "f64": 40, "u8": 100}
+
+
+def _rule_edges(kind):
+    """Sizes around the lines of the 2-way rule: eight waves to four, and the last of
+    the small tiles to the first of the 64 x 64 ones."""
+    import librules
+    import torch
+    dt = {"f32": torch.float32, "f16": torch.float16, "f64": torch.float64,
+          "u8": torch.uint8}[kind]
+
+    def waves(n_v):
+        return librules.pairs_2way(dt, RULE_N_F[kind], n_v)[0]
+    eight = max(n for n in range(2, 1200) if waves(n) == 8)
+    last = max(n for n in range(eight, 4000) if waves(n))
+    assert [waves(n) for n in (eight, eight + 1, last, last + 1)] == [8, 4, 4, 0]
+    chunks = librules.pairs_2way(dt, RULE_N_F[kind], last)[1]
+    assert (chunks > 1) == (kind in ("f32", "f16"))   # the sums ride along, or not
+    return [eight, eight + 1, last, last + 1]
+
+
+@pytest.mark.parametrize("kind", ["f32", "f16", "f64", "u8"])
+@pytest.mark.parametrize("k", range(4))
+def test_2way_at_the_lines_of_the_rule(kind, k):
+    """Against the oracle, the sums inside; the shards of a call together write its
+    bits once, whether the sums are given or not."""
+    import torch
+    from paper_1705_08210_amd import ps
+    n_v = _rule_edges(kind)[k]
+    V = _data(kind, n_v, RULE_N_F[kind], seed=n_v)
+    announce(f"small rule line {kind} {n_v}x{RULE_N_F[kind]}")
+    Vd = to_dev(V)
+    full, n2 = ps.ps2(Vd, want_n2=True)
+    _check(host(full), oracle.c2_all(V), kind, "c2")
+    s, _ = ps.vector_sums(Vd)
+    for given in (None, s):
+        union, nun = torch.full_like(full, float("nan")), torch.full_like(n2, -1)
+        for r in range(3):
+            before = union.clone()
+            ps.ps2_shard(Vd, r, 3, s=given, c2=union, n2=nun)
+            written = torch.isnan(before)
+            assert bool((union[~written] == before[~written]).all())
+        assert np.array_equal(host(union).view(np.uint32), host(full).view(np.uint32))
+        assert bool((nun == n2).all())
