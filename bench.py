@@ -170,6 +170,7 @@ _MFMA_SOURCES = ["ps_internal.h", "mfma_tile.h", "mfma.hip", "policy.hip"]
 _BITS_SOURCES = ["ps_internal.h", "mfma_tile.h", "bitplane.hip", "policy.hip"]
 KERNEL_SOURCES = {
     "ps_mg2_kernel": _VALU_SOURCES,
+    "ps_sm2_kernel": _VALU_SOURCES,
     "ps_mg3f_kernel": _VALU_SOURCES,
     "ps_mgb_kernel": _VALU_SOURCES,
     "ps_mfma2_lv_kernel": _MFMA_SOURCES,
@@ -512,6 +513,8 @@ def measure(args, wl, K, W, with_cpu=True):
         else:                        # min + add per comparison
             dtype, bound, ops_per_cmp, peak = "f32", "alu", 2.0, FP32_LANE_OPS_TOPS
             kernel = "ps_mg2_kernel"
+        if path == "valu" and wl == "uniform_1024x256" and not args.tile:
+            kernel = "ps_sm2_kernel"   # 32 x 32 tiles (few workgroups otherwise)
         config = {"workload": wl, "way": 2, "n_f": n_f, "n_v": n_v, "path": path}
         if N > 1:
             config["shard"] = f"0 of {N}"
@@ -585,7 +588,10 @@ def measure(args, wl, K, W, with_cpu=True):
 
         cmp = n_f * math.comb(n_v, 3)
         path = resolved_path(args, V, 3)
-        if path in ("mfma_fp4", "bits"):   # planes of bits: `levels` MACs per comparison
+        if path == "bits" and args.tile:   # v_and + v_bcnt per 32 comparisons
+            dtype, bound, ops_per_cmp, peak = "b1", "alu", 2.0 / 32, HALF_RATE_OPS_TOPS
+            kernel = "ps_mg3f_kernel"
+        elif path in ("mfma_fp4", "bits"):   # planes of bits: `levels` MACs per comparison
             dtype, bound, ops_per_cmp, peak = "fp4", "mfma", 2.0 * levels, FP4_MFMA_PEAK_TOPS
             kernel = "ps_bp3_kernel"
         elif path == "mfma":
