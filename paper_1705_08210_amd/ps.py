@@ -152,16 +152,12 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
 
 
-def _room(query, dt: int, o: Opts, device) -> torch.Tensor:
-    """The workspace of a call, query(opts) bytes.  Where the device has no room for
-    the planes of bits that path AUTO takes for integer levels, the workspace of
-    the paths without them, which the call then runs on."""
-    try:
-        return _workspace(query(o), device)
-    except torch.OutOfMemoryError:
-        if dt != PS_U8 or o.path != PATH["auto"]:
-            raise
-        return _workspace(query(Opts(o.acc, PATH["valu"], o.levels, o.tile)), device)
+def _less_room(dt: int, o: Opts) -> Opts:
+    """Out of memory for a call's workspace: the options whose (smaller) workspace
+    path AUTO on integer levels also runs with, without its planes of bits."""
+    if dt != PS_U8 or o.path != PATH["auto"]:
+        raise   # noqa: PLE0704 -- called while the OutOfMemoryError is handled
+    return Opts(o.acc, PATH["valu"], o.levels, o.tile)
 
 
 def n2_dtype(V_dtype) -> torch.dtype:
@@ -196,8 +192,13 @@ def ps2(V: torch.Tensor, s: torch.Tensor | None = None, want_c2: bool = True,
         if want_n2 and n2 is None:
             n2 = torch.empty(m, dtype=n2_dtype(V.dtype), device=V.device)
         o = _opts(acc, path, levels, tile)
-        ws = _room(lambda q: lib.ps2_workspace_size(dt, n_f, n_v, int(s is not None),
-                                                    ctypes.byref(q)), dt, o, V.device)
+        given = int(s is not None)
+        try:
+            ws = _workspace(lib.ps2_workspace_size(dt, n_f, n_v, given, ctypes.byref(o)),
+                            V.device)
+        except torch.OutOfMemoryError:
+            ws = _workspace(lib.ps2_workspace_size(dt, n_f, n_v, given,
+                                                   ctypes.byref(_less_room(dt, o))), V.device)
         _check(lib.ps2_compute(V.data_ptr(), dt, n_f, n_v, ld, _ptr(s), _ptr(c2), _ptr(n2),
                                ws.data_ptr(), ws.numel(), ctypes.byref(o), _stream(stream)))
     return c2, n2
@@ -231,6 +232,14 @@ def stage_size(n_v: int, j_begin: int, j_end: int) -> int:
     return int(lib.ps3_stage_size(n_v, j_begin, j_end))
 
 
+def _workspace3(dt, n_f, n_v, s, n2, j_begin, j_end, o, device):
+    args = dt, n_f, n_v, int(s is not None), int(n2 is not None), j_begin, j_end
+    try:
+        return _workspace(lib.ps3_workspace_size(*args, ctypes.byref(o)), device)
+    except torch.OutOfMemoryError:
+        return _workspace(lib.ps3_workspace_size(*args, ctypes.byref(_less_room(dt, o))), device)
+
+
 def ps3(V: torch.Tensor, s: torch.Tensor | None = None, n2: torch.Tensor | None = None,
         j_begin: int = 1, j_end: int | None = None, acc="auto", tile=0,
         c3: torch.Tensor | None = None, stream=None, path="auto",
@@ -246,9 +255,7 @@ def ps3(V: torch.Tensor, s: torch.Tensor | None = None, n2: torch.Tensor | None 
         if c3 is None:
             c3 = torch.empty(m, dtype=torch.float32, device=V.device)
         o = _opts(acc, path, levels, tile)
-        ws = _room(lambda q: lib.ps3_workspace_size(dt, n_f, n_v, int(s is not None),
-                                                    int(n2 is not None), j_begin, j_end,
-                                                    ctypes.byref(q)), dt, o, V.device)
+        ws = _workspace3(dt, n_f, n_v, s, n2, j_begin, j_end, o, V.device)
         _check(lib.ps3_compute(V.data_ptr(), dt, n_f, n_v, ld, _ptr(s), _ptr(n2), j_begin,
                                j_end, c3.data_ptr() if m > 0 else None, ws.data_ptr(),
                                ws.numel(), ctypes.byref(o), _stream(stream)))
@@ -376,9 +383,7 @@ class Plan3:
         self.V, self.s, self.n2 = V, s, n2
         self.c3 = c3 if c3 is not None else torch.empty(m, dtype=torch.float32, device=V.device)
         o = _opts(acc, path, levels, tile)
-        self.ws = _room(lambda q: lib.ps3_workspace_size(dt, n_f, n_v, int(s is not None),
-                                                         int(n2 is not None), j_begin, j_end,
-                                                         ctypes.byref(q)), dt, o, V.device)
+        self.ws = _workspace3(dt, n_f, n_v, s, n2, j_begin, j_end, o, V.device)
         self._home = torch.cuda.current_stream(V.device)
         h = P()
         _check(lib.ps_plan_create_3way(ctypes.byref(h), V.data_ptr(), dt, n_f, n_v, ld, _ptr(s),
