@@ -1,5 +1,5 @@
 // mfma_tile.h -- pieces shared by the matrix-core tile kernels (mfma.hip: int8
-// and fp4 thermometer planes of bytes; bitplane.hip: planes of bits): launch
+// thermometer planes of bytes; bitplane.hip: planes of bits on fp4): launch
 // arguments, the LDS stage layout and hand-over, and the 3-way epilogues of
 // the split tiling.
 #pragma once

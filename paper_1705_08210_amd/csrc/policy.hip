@@ -53,14 +53,21 @@ int choose_cfg(int32_t dt, int32_t way, int32_t path, int64_t n_f, int64_t n_v,
 
 // The 32 x 32 field-split tiles pay while the 64 x 64 tiles (x field chunks)
 // leave the chip short of workgroups; past that their double operand traffic
-// per output shows.  Whole calls, us, 64 x 64 / 32 x 32:
-//   FP32 (split over field chunks): 1001 fields, 1024 vectors 51 / 40 (1088
-//     items), 1500 85 / 75, 2048 121 / 114; 12000 fields, 256 vectors 75 / 65
-//     (940 items), 512 122 / 127 (2052 items)
-//   FP64 (never split): 4096 fields, 700 vectors 529 / 119, 2048 983 / 730 (528
-//     tiles), 3000 1518 / 1407
-//   uint8: 4096 fields, 700 vectors 81 / 24, 2048 138 / 105; 1001 fields, 1500
-//     40 / 35, 2048 50 / 52
+// per output shows, the sooner the more fields a tile sums at a time.  Whole calls,
+// us, 64 x 64 / 32 x 32 with four waves:
+//   FP32, FP16 (split over field chunks; line 1200 items).  Below: 1001 fields, 1024
+//     vectors 48 / 38 (1088 items; FP16 39 / 35); 12000 fields, 256 vectors 74 / 63
+//     (750; FP16 49 / 38).  Above: 12000 fields, 384 vectors 99 / 94 (1575), 512
+//     121 / 127 (1944); 4096 fields, 700 vectors 78 / 81 (2112); but 1001 fields,
+//     1500 vectors 77 / 70 (2100), 2048 113 / 108; 300 fields, 2500 vectors 70 / 65
+//   FP64 (never split; line 560 tiles).  Below: 5000 fields, 2048 vectors 1187 / 888
+//     (528).  Above: 413 fields, 3000 vectors 167 / 172 (1128), 5830 499 / 603; but
+//     5000 fields, 2500 vectors 1496 / 1254 (820), 4096 3131 / 3063, 5000 4425 / 4518
+//   uint8 (never split; line 300 tiles below 2048 fields, else 560).  Below: 1001
+//     fields, 1500 vectors 39 / 34 (300); 4096 fields, 2048 vectors 137 / 102 (528).
+//     Above: 1001 fields, 2048 vectors 49 / 51; but 4096 fields, 3000 203 / 188
+// The number of items alone does not separate the two sides: each line lies where no
+// depth of fields loses yet, and leaves up to a fifth beyond it to a finer rule.
 // Eight waves while all workgroups find a CU of their own (FP64, 4096 fields:
 // 700 vectors 119 against 162 with four, 1024 324 against 276).
 int small2(int32_t dt, int64_t n_f, int64_t n_v, int cfg, int32_t nchunks, const ps_opts* o) {
@@ -176,10 +183,13 @@ static bool mfma_can(int path, int way, int64_t n_f, int64_t n_v, int levels, in
 }
 
 // AUTO keeps triangles of up to this many vectors on a path without a plane
-// workspace: the VALU path with its small tiles (256-row matrix-core tiles leave
-// most of the chip idle: three levels, int8 / VALU, us: 4096 fields, 512 vectors
-// 115 / 24; 12000 fields, 1024 vectors 220 / 117), int8 only where the byte
-// sums do not fit 32 bits.
+// workspace, so that their size query stays 0 (with the sums given): the VALU path
+// with its small tiles, int8 only where the byte sums do not fit 32 bits.  What that
+// costs or gains, us, VALU / planes of bits: three levels, 4096 fields, 512 vectors
+// 22 / 19, 1023 44 / 20; 12000 fields, 512 52 / 44, 1023 114 / 47; one level, 12000
+// fields, 1023 114 / 21; fifteen levels, 12000 fields, 512 52 / 182, 1023 114 / 181;
+// 300 fields 14 / 14.  (int8, three levels: 4096 fields, 512 vectors 115; 12000
+// fields, 1024 vectors 220: its 256-row tiles leave most of the chip idle.)
 static constexpr int64_t kBpMinVectors = 1024;
 
 // A tuned entry for (dt, way, path) covering the shape, or -1.
