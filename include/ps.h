@@ -368,8 +368,8 @@ ps_status ps_tune_register(int32_t dtype, int32_t way, int32_t path,
                            int64_t nv_hi, int32_t idx);
 /* The path (a ps_path value other than AUTO) that ps2_compute (way 2) or
  * ps3_compute (way 3) takes for these arguments: opts.path itself unless it
- * is AUTO, else the library's choice (policy and tuning table).  -1 for an
- * unknown dtype or way. */
+ * is AUTO, else the library's choice (policy and tuning table) with a workspace
+ * of the size query.  -1 for an unknown dtype or way. */
 int32_t ps_path_choice(int32_t dtype, int32_t way, int64_t n_f, int64_t n_v, int64_t ld,
                        const ps_opts* opts);
 
